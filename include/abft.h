@@ -208,10 +208,10 @@ int abft_quantize_encode(const abft_problem *p, const float *A32, int64_t lda32,
  * B_f (F64, F32; for BF16 / FP8 into ws, in binary32), summing in binary64
  * and rounding once, and writes the
  * per-row / per-column statistics the thresholds are built from into ws.
- * HBM-bound: A and B are read once each when k / (16 / element size) is a
- * multiple of 64 (the row statistics are taken in the same pass); otherwise,
- * and for the statistical thresholds' weighted row sums of A (whose weights
- * exist only after B's encode), a second pass reads the operand again.
+ * HBM-bound: A and B are read once each (the row statistics are taken in the
+ * same pass), except for the statistical thresholds' weighted row sums, whose
+ * weights come from the other operand's encode: A's rows, and B's when they
+ * are few, are read again in a second pass.
  */
 int abft_encode(const abft_problem *p, void *A_f, void *B_f, void *ws, size_t ws_bytes, void *stream);
 

@@ -26,9 +26,29 @@ int64_t group_partitions(int64_t G, int64_t b, int64_t cols) {
     return P;
 }
 
-bool rows_fused(const abft_problem *p) {
-    const int64_t vpe = 16 / (int64_t)dtype_size(p->dtype);
-    return (p->tau_mode == ABFT_TAU_DET || p->tau_mode == ABFT_TAU_STAT) && (p->k / vpe) % 64 == 0;
+EncSplit enc_split(int64_t R, int64_t b, int64_t k, int V) {
+    EncSplit e;
+    const int64_t kv = k / V, G = R / b;
+    // 64 lanes read 1 KB of a row at once; where that leaves over a tenth of the lanes past the last column, 16 do
+    e.cw = (kv % 64 == 0 || kv >= 640) ? 64 : 16;
+    const int64_t rw = 256 / e.cw;
+    e.strips = (kv + e.cw - 1) / e.cw;
+    const int64_t direct = e.strips * ((b + rw - 1) / rw);
+    // whole residues per lane where few groups or enough residues make it short, else enough partitions for
+    // about 16 blocks per CU, each with at least four rows per row lane (what a lane requests together)
+    e.direct = G <= 16 || direct >= 1024;
+    if (e.direct) {
+        e.P = 1;
+        e.chunk = G;
+        e.blocks = direct;
+    } else {
+        const int64_t want = std::max<int64_t>(1, 4096 / (e.strips * b));
+        e.chunk = std::min(G, std::max((G + want - 1) / want, 4 * rw));
+        e.P = (G + e.chunk - 1) / e.chunk;
+        e.blocks = e.strips * b * e.P;
+    }
+    e.tail_slots = std::max(e.strips, (k + 63) / 64);
+    return e;
 }
 
 WsLayout ws_layout(const abft_problem *p) {
@@ -49,21 +69,19 @@ WsLayout ws_layout(const abft_problem *p) {
     L.acs = take(cs_in_ws(p->dtype) ? sizeof(float) * g.br * g.k : 8);
     L.bcs = take(cs_in_ws(p->dtype) ? sizeof(float) * g.bc * g.k : 8);
     L.scale = take(16);
-    // partial sums: encode A (2 stats), encode B (2 stats), verify columns (1);
-    // encode threads own 16 bytes of a row each
-    int64_t vpe = 16 / (int64_t)dtype_size(p->dtype);
-    int64_t pa = group_partitions(g.Gr, g.br, g.k / vpe);
-    int64_t pb = group_partitions(g.Gc, g.bc, g.k / vpe);
+    // partial sums: encode A (2 stats), encode B (2 stats), verify columns (1, in A's)
+    const EncSplit ea = enc_split(g.m, g.br, g.k, enc_vec(p->dtype)), eb = enc_split(g.n, g.bc, g.k, enc_vec(p->dtype));
     int64_t pc = std::max(group_partitions(g.Gr, g.br, g.N), group_partitions(g.Gr, g.br, (g.N + 1) / 2));
     pc = std::max(pc, group_partitions(g.Gr, g.br, (g.N + 3) / 4));
     size_t need = 0;
-    if (pa > 1) need = std::max(need, (size_t)(pa * g.br * g.k * 2));
-    if (pb > 1) need = std::max(need, (size_t)(pb * g.bc * g.k * 2));
+    if (!ea.direct) need = (size_t)(ea.P * g.br * g.k * 2);
     if (pc > 1) need = std::max(need, (size_t)(pc * g.br * g.N));
     L.partial_bytes = sizeof(double) * need;
     L.partial = take(L.partial_bytes > 0 ? L.partial_bytes : 8);
-    // fused row statistics: the larger operand's data rows plus its checksum and group rows, k / 64 slots each
-    L.rowpart = take(rows_fused(p) ? sizeof(double) * (std::max(g.m, g.n) + 2 * std::max(g.br, g.bc)) * (g.k / 64) : 8);
+    L.partial_b = take(eb.direct ? 8 : sizeof(double) * (size_t)(eb.P * g.bc * g.k * 2));
+    // fused row statistics: the data rows' strips, then the checksum and group rows' slots
+    L.rowpart = take(sizeof(double) * (size_t)(g.m * ea.strips + 2 * g.br * ea.tail_slots));
+    L.rowpart_b = take(sizeof(double) * (size_t)(g.n * eb.strips + 2 * g.bc * eb.tail_slots));
     // one-pass re-read verification (b = 1): column sums per kVerifyPartRows-row tile, row sums per 128-column
     // (binary64 C) or 256-column (binary32 C) tile
     const bool b1 = g.br == 1 && g.bc == 1;

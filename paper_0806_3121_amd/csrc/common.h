@@ -209,11 +209,11 @@ struct WsLayout {
     size_t grpA, grpB;               // per-residue group sums of |A| (or A^2) and of |B| (double, br*k / bc*k)
     size_t acs, bcs;                 // binary32 checksum rows of low-precision operands (float, br*k / bc*k)
     size_t scale;                    // FP8 per-tensor scale exponents and amax scratch (4 x int32)
-    size_t partial;                  // two-level reduction partials (double)
+    size_t partial, partial_b;       // two-level reduction partials (double): A's encode and the verification; B's encode
     size_t fused_c, fused_r;         // product-epilogue partial sums for b = 1 (double)
     size_t chain_a, chain_w;         // chained products: inherited threshold term chain_a[r] chain_w[j]
     size_t chain_cs;                 // chained products: the recomputed checksum rows (discarded; br x k elements)
-    size_t rowpart;                  // fused row statistics: per-row partial sums
+    size_t rowpart, rowpart_b;       // fused row statistics: per-row partial sums of A, of B
     size_t vpart_c, vpart_r;         // one-pass re-read verification for b = 1: tile partial sums (double)
     size_t fused_tag;                // owner of the fused partials: fused_key() of the last fused product, else 0
     size_t report;                   // abft_report
@@ -222,10 +222,24 @@ struct WsLayout {
 };
 WsLayout ws_layout(const abft_problem *p);
 
-// Det or statistical thresholds with k / (16 / size) a multiple of 64: the
-// encode pass also produces the row statistics (rows_fused), from per-row
-// partials in ws.
-bool rows_fused(const abft_problem *p);
+// Columns per lane of the encode pass, by element type: 16 bytes, or 8 for the
+// one-byte type, whose 16 columns would need 64 registers of sums.
+template <typename T> constexpr int kEncVec = sizeof(T) == 1 ? 8 : 16 / (int)sizeof(T);
+inline int enc_vec(int dt) { return dt == ABFT_FP8_E4M3 ? 8 : 16 / (int)dtype_size(dt); }
+
+// How the encode pass splits one operand (R rows in R / b groups, k columns,
+// V columns per lane) over blocks of 256 threads.
+struct EncSplit {
+    int cw;                 // lanes across a strip of columns: 64, or 16 where 64 would leave many idle
+    bool direct;            // each row lane sums whole residues; else a block sums one of P partitions
+    int64_t strips;         // ceil(k / (V cw))
+    int64_t P, chunk;       // partitions of the groups, groups per partition
+    int64_t blocks;
+    int64_t tail_slots;     // row-statistic partials per checksum or group row
+};
+EncSplit enc_split(int64_t R, int64_t b, int64_t k, int V);
+// B's size from which its row statistics are worth a serial pass (see encode_typed).
+constexpr int64_t kEncRereadBytes = int64_t(48) << 20;
 
 // Number of partitions used for the row-group sums of a (G groups, b residues, cols) sum.
 int64_t group_partitions(int64_t G, int64_t b, int64_t cols);

@@ -64,10 +64,6 @@ __device__ inline double record(abft_report *rep, bool col, int64_t a, int64_t b
     return 0.0;
 }
 
-__global__ __launch_bounds__(kThreads) void k_fill_zero(double *x, int64_t n) {
-    for (int64_t t = threadIdx.x; t < n; t += kThreads) x[t] = 0.0;
-}
-
 __global__ void k_report_init(abft_report *rep) {
     uint64_t *w = (uint64_t *)rep;
     const int nw = sizeof(abft_report) / 8;
@@ -106,39 +102,44 @@ __device__ inline double row_term(int mode, double x, double w) {
     return mode == ROW_W ? x2 * w : (mode == ROW_L4SQ ? x2 * x2 : x2);
 }
 
-// Row partials of the fused row statistics: with rp set, a wave whose 64 lanes
-// hold 64 consecutive vectors of one row also writes the sum of that 64-vector
-// chunk's terms, rp[row * rps + chunk]: data row g*b + r and checksum row R + r
-// (statistic rmode, weights rw for ROW_W), group-statistic row R + b + r
-// (ROW_L2).  The host sets rp only when k / V is a multiple of 64, so every
-// wave is whole and shares r.
-__device__ inline void row_partial(double *rp, int64_t rps, int64_t row, int64_t chunk, double q2) {
-    q2 = wave_sum(q2);
-    if (threadIdx.x % kWave == 0) rp[row * rps + chunk] = q2;
-}
-
 // Where the encode pass takes an operand's values from: the stored operand,
 // or binary32 values quantized to bfloat16 on the way (round to nearest even),
-// which are written to the operand's storage and used as stored.  load(row, l0, v) fills the V values
-// X[row, l0 .. l0+V) as binary64.
+// which are written to the operand's storage and used as stored.  fetch
+// requests the V values X[row, l0 .. l0+V) (raw words, so that several rows
+// are in flight), take fills them in as binary64.
 template <typename T> struct SrcStored {
+    static constexpr int V = kEncVec<T>;
+    typedef typename std::conditional<V * sizeof(T) == 16, v4u32, uint64_t>::type Raw;
     const T *X;
     int64_t ld;
-    __device__ void load(int64_t row, int64_t l0, double *v) const { vec16<T>::load(X + row * ld + l0, v); }
+    __device__ Raw fetch(int64_t row, int64_t l0) const { return *(const Raw *)(X + row * ld + l0); }
+    __device__ void take(const Raw &w, int64_t, int64_t, double *v) const {
+        if constexpr (V * sizeof(T) == 16) {
+            vec16<T>::widen(w, v);
+        } else {
+            static_assert(sizeof(T) == 1 && V == 8, "two E4M3 words");
+            e4m3x4_to_f64((uint32_t)w, v);
+            e4m3x4_to_f64((uint32_t)(w >> 32), v + 4);
+        }
+    }
 };
 struct SrcQuantBf16 {
+    static constexpr int V = kEncVec<uint16_t>;
+    typedef float v4 __attribute__((ext_vector_type(4)));
+    struct Raw { v4 x0, x1; };
     const float *X;
     int64_t ldx;
     uint16_t *Q;
     int64_t ldq;
-    __device__ void load(int64_t row, int64_t l0, double *v) const {
-        typedef float v4 __attribute__((ext_vector_type(4)));
-        const v4 x0 = *(const v4 *)(X + row * ldx + l0), x1 = *(const v4 *)(X + row * ldx + l0 + 4);
+    __device__ Raw fetch(int64_t row, int64_t l0) const {
+        return Raw{*(const v4 *)(X + row * ldx + l0), *(const v4 *)(X + row * ldx + l0 + 4)};
+    }
+    __device__ void take(const Raw &w, int64_t row, int64_t l0, double *v) const {
         uint16_t h[8];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            h[q] = f32_to_bf16_rne(x0[q]);
-            h[4 + q] = f32_to_bf16_rne(x1[q]);
+            h[q] = f32_to_bf16_rne(w.x0[q]);
+            h[4 + q] = f32_to_bf16_rne(w.x1[q]);
         }
         v4u32 o;
 #pragma unroll
@@ -148,137 +149,223 @@ struct SrcQuantBf16 {
         for (int q = 0; q < 8; ++q) v[q] = (double)bf16_to_f32(h[q]);
     }
 };
-// Each thread owns V = 16/sizeof(T) consecutive columns l (one 16-byte load per
-// row); rows of X are 16-byte aligned and k is a multiple of V.  STAT: the
-// statistical group statistic (sum of squares, else sum of magnitudes); RM:
-// the row statistic of the fused row partials, kRowNone for none (rp unused).
-constexpr int kRowNone = -1;
-template <typename T, typename TC, class Src, bool STAT, int RM>
-__global__ __launch_bounds__(kThreads) void k_encode_direct(Src src, int64_t b, int64_t G, int64_t k, TC *CS,
-                                                            int64_t ldcs, double *grp, double *rp, int64_t rps,
-                                                            const double *rw) {
-    constexpr int V = vec16<T>::N;
-    const int64_t kv = k / V, total = b * kv;
-    for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < total; t += (int64_t)gridDim.x * kThreads) {
-        int64_t r = t / kv, l0 = (t - r * kv) * V;
-        const int64_t chunk = l0 / (kWave * V);
-        double s[V], ss[V], wv[V];
-#pragma unroll
-        for (int q = 0; q < V; ++q) {
-            s[q] = ss[q] = 0.0;
-            wv[q] = RM == ROW_W ? rw[l0 + q] : 0.0;
-        }
-        for (int64_t g = 0; g < G; ++g) {
+
+// One operand in the encode pass.  A block of 256 threads covers a strip of
+// CW column vectors (CW = 64 or 16 lanes of V columns) with 256 / CW row
+// lanes; how the row lanes and blocks share the groups is EncSplit's choice.
+//   rp:  partials of the data rows' statistic, rp[row * strips + strip]
+//   rpt: partials of the checksum and group rows' statistics, rpt[row * nt + .],
+//        rows 0 .. b-1 the checksum rows, b .. 2b-1 the group rows
+template <class Src, typename TC> struct EncSide {
+    Src src;
+    int64_t b, G, k, strips, P, chunk;
+    double *part;
+    TC *CS;
+    int64_t ldcs;
+    double *grp, *rp, *rpt;
+    int64_t nt;
+    const double *rw;
+};
+constexpr int kRowNone = -1;     // no fused row statistic
+constexpr int kEncRows = 4;      // rows requested together per lane
+
+// Sums of rows g*b + r, g = g0, g0 + step, ... < g1, over the strip's columns
+// of one lane (V sums and V group statistics), and the rows' statistic RM
+// folded over the CW lanes of the strip: four rows' partials by a
+// reduce-scatter (2 + 1 exchanges, then within CW / 4 lanes).  Lanes past the
+// last column (ok false) take no loads and add zeros.
+template <int CW, class Src, typename TC, bool STAT, int RM>
+__device__ __attribute__((always_inline)) inline void enc_rows(const EncSide<Src, TC> &o, int64_t r, int64_t g0,
+                                                               int64_t g1, int64_t step, int64_t strip, int c, bool ok,
+                                                               int64_t l0, const double *wv, double *s, double *ss) {
+    constexpr int V = Src::V, U = kEncRows;
+    auto add = [&](const typename Src::Raw &w, int64_t row) {
+        double q2 = 0.0;
+        if (ok) {
             double v[V];
-            src.load(g * b + r, l0, v);
-            double q2 = 0.0;
+            o.src.take(w, row, l0, v);
 #pragma unroll
             for (int q = 0; q < V; ++q) {
                 s[q] += v[q];
                 ss[q] += STAT ? v[q] * v[q] : fabs(v[q]);
                 if constexpr (RM != kRowNone) q2 += row_term(RM, v[q], wv[q]);
             }
-            if constexpr (RM != kRowNone) row_partial(rp, rps, g * b + r, chunk, q2);
         }
-        double c2 = 0.0, g2 = 0.0;
+        return q2;
+    };
+    int64_t g = g0;
+    for (; g + (U - 1) * step < g1; g += U * step) {
+        typename Src::Raw w[U];
+        if (ok) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) w[u] = o.src.fetch((g + u * step) * o.b + r, l0);
+        }
+        double q[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) q[u] = add(w[u], (g + u * step) * o.b + r);
+        if constexpr (RM != kRowNone) {
+            static_assert(U == 4, "reduce-scatter of four rows");
+            const bool hi = c & (CW / 2), lo = c & (CW / 4);
+            double k0 = hi ? q[2] : q[0], k1 = hi ? q[3] : q[1];
+            k0 += __shfl_xor(hi ? q[0] : q[2], CW / 2);
+            k1 += __shfl_xor(hi ? q[1] : q[3], CW / 2);
+            double x = lo ? k1 : k0;
+            x += __shfl_xor(lo ? k0 : k1, CW / 4);
+#pragma unroll
+            for (int off = CW / 8; off > 0; off >>= 1) x += __shfl_xor(x, off);
+            if (c % (CW / 4) == 0) o.rp[((g + (c / (CW / 4)) * step) * o.b + r) * o.strips + strip] = x;
+        }
+    }
+    for (; g < g1; g += step) {
+        typename Src::Raw w;
+        if (ok) w = o.src.fetch(g * o.b + r, l0);
+        double x = add(w, g * o.b + r);
+        if constexpr (RM != kRowNone) {
+#pragma unroll
+            for (int off = CW / 2; off > 0; off >>= 1) x += __shfl_xor(x, off);
+            if (c == 0) o.rp[(g * o.b + r) * o.strips + strip] = x;
+        }
+    }
+}
+
+template <class Src, int RM> __device__ inline void enc_weights(const double *rw, int64_t l0, double *wv) {
+#pragma unroll
+    for (int q = 0; q < Src::V; ++q) wv[q] = RM == ROW_W ? rw[l0 + q] : 0.0;
+}
+
+// Direct: each row lane owns a residue and sums all its groups, so the sums
+// are finished here (no partials).  Blocks [0, na) work on x, the rest on y.
+template <int CW, class Src, typename TC, bool STAT, int RM>
+__global__ __launch_bounds__(kThreads) void k_encode_direct(EncSide<Src, TC> x, EncSide<Src, TC> y, unsigned na) {
+    constexpr int V = Src::V, RW = kThreads / CW;
+    const EncSide<Src, TC> &o = blockIdx.x < na ? x : y;
+    const int64_t idx = blockIdx.x < na ? blockIdx.x : blockIdx.x - na;
+    const int64_t strip = idx % o.strips, r = idx / o.strips * RW + threadIdx.x / CW;
+    if (r >= o.b) return;
+    const int c = threadIdx.x % CW;
+    const int64_t kv = o.k / V, cv = strip * CW + c, l0 = min(cv, kv - 1) * V;
+    const bool ok = cv < kv;
+    double s[V] = {}, ss[V] = {}, wv[V];
+    enc_weights<Src, RM>(o.rw, l0, wv);
+    enc_rows<CW, Src, TC, STAT, RM>(o, r, 0, o.G, 1, strip, c, ok, l0, wv, s, ss);
+    double c2 = 0.0, g2 = 0.0;
+    if (ok) {
 #pragma unroll
         for (int q = 0; q < V; ++q) {
-            finish_encode<TC>(s[q], ss[q], STAT, CS + r * ldcs + l0 + q, grp + r * k + l0 + q);
+            finish_encode<TC>(s[q], ss[q], STAT, o.CS + r * o.ldcs + l0 + q, o.grp + r * o.k + l0 + q);
             if constexpr (RM != kRowNone) {
-                const double c = (double)(TC)s[q], gv = STAT ? ss[q] + c * c : ss[q];
-                c2 += row_term(RM, c, wv[q]);
+                const double cs = (double)(TC)s[q], gv = STAT ? ss[q] + cs * cs : ss[q];
+                c2 += row_term(RM, cs, wv[q]);
                 g2 += gv * gv;
             }
         }
-        if constexpr (RM != kRowNone) {
-            row_partial(rp, rps, G * b + r, chunk, c2);
-            row_partial(rp, rps, G * b + b + r, chunk, g2);
+    }
+    if constexpr (RM != kRowNone) {
+#pragma unroll
+        for (int off = CW / 2; off > 0; off >>= 1) {
+            c2 += __shfl_xor(c2, off);
+            g2 += __shfl_xor(g2, off);
+        }
+        if (c == 0) {
+            o.rpt[r * o.nt + strip] = c2;
+            o.rpt[(o.b + r) * o.nt + strip] = g2;
         }
     }
 }
 
-template <typename T, class Src, bool STAT, int RM>
-__global__ __launch_bounds__(kThreads) void k_encode_partial(Src src, int64_t b, int64_t G, int64_t k, int64_t P,
-                                                             int64_t chunk, double *part, double *rp, int64_t rps,
-                                                             const double *rw) {
-    constexpr int V = vec16<T>::N;
-    const int64_t kv = k / V, rel = b * k, total = P * b * kv;
-    for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < total; t += (int64_t)gridDim.x * kThreads) {
-        int64_t p = t / (b * kv), q = t - p * (b * kv);
-        int64_t r = q / kv, l0 = (q - r * kv) * V;
-        int64_t g0 = p * chunk, g1 = min(G, g0 + chunk);
-        const int64_t lc = l0 / (kWave * V);
-        double s[V], ss[V], wv[V];
+// Partitioned: a block sums one partition (chunk groups) of one residue, its
+// row lanes taking the groups in turn and adding up through LDS in lane order.
+// HBM-bound; the block, not the thread, owns a partition, so the partials are
+// a small share of the operand (a thread per partition wrote more bytes of
+// partials than it read of a 3000 x 2056 bfloat16 operand: both operands of a
+// 3000 x 5003 x 2056 product took 36 + 41 us here and 141 + 141 us in the
+// finish, now 23 and 5; 16384 x 16384 quantized from binary32: 331 + 39 us,
+// now 321 + 11, 5.0 TB/s, the rate of a large copy).
+template <int CW, class Src, typename TC, bool STAT, int RM>
+__global__ __launch_bounds__(kThreads) void k_encode_partial(EncSide<Src, TC> x, EncSide<Src, TC> y, unsigned na) {
+    constexpr int V = Src::V, RW = kThreads / CW;
+    __shared__ double sh[RW][CW * V];
+    const EncSide<Src, TC> &o = blockIdx.x < na ? x : y;
+    const int64_t idx = blockIdx.x < na ? blockIdx.x : blockIdx.x - na;
+    const int64_t strip = idx % o.strips, pr = idx / o.strips, r = pr % o.b, p = pr / o.b;
+    const int c = threadIdx.x % CW, w = threadIdx.x / CW;
+    const int64_t kv = o.k / V, cv = strip * CW + c, l0 = min(cv, kv - 1) * V;
+    const int64_t g0 = p * o.chunk, g1 = min(o.G, g0 + o.chunk);
+    double s[V] = {}, ss[V] = {}, wv[V];
+    enc_weights<Src, RM>(o.rw, l0, wv);
+    enc_rows<CW, Src, TC, STAT, RM>(o, r, g0 + w, g1, RW, strip, c, cv < kv, l0, wv, s, ss);
+    const int64_t rel = o.b * o.k;
+    double *out = o.part + 2 * p * rel + r * o.k + strip * CW * V;
+    auto combine = [&](const double *v, double *dst) {
 #pragma unroll
-        for (int e = 0; e < V; ++e) {
-            s[e] = ss[e] = 0.0;
-            wv[e] = RM == ROW_W ? rw[l0 + e] : 0.0;
-        }
-        for (int64_t g = g0; g < g1; ++g) {
-            double v[V];
-            src.load(g * b + r, l0, v);
-            double q2 = 0.0;
+        for (int q = 0; q < V; ++q) sh[w][q * CW + c] = v[q];
+        __syncthreads();
+        for (int t = threadIdx.x; t < CW * V; t += kThreads) {
+            double a = 0.0;
 #pragma unroll
-            for (int e = 0; e < V; ++e) {
-                s[e] += v[e];
-                ss[e] += STAT ? v[e] * v[e] : fabs(v[e]);
-                if constexpr (RM != kRowNone) q2 += row_term(RM, v[e], wv[e]);
-            }
-            if constexpr (RM != kRowNone) row_partial(rp, rps, g * b + r, lc, q2);
+            for (int u = 0; u < RW; ++u) a += sh[u][(t % V) * CW + t / V];
+            if (strip * CW * V + t < o.k) dst[t] = a;
         }
-#pragma unroll
-        for (int e = 0; e < V; ++e) {
-            part[(2 * p) * rel + r * k + l0 + e] = s[e];
-            part[(2 * p + 1) * rel + r * k + l0 + e] = ss[e];
-        }
-    }
+        __syncthreads();
+    };
+    combine(s, out);
+    combine(ss, out + rel);
 }
 
+// Finish of the partitioned sums: a block takes 64 columns of one residue, its
+// four waves every fourth partition (four running sums each, eight loads in
+// flight), added through LDS in a fixed order.
+template <typename TC> struct FinSide {
+    int64_t b, k, P;
+    const double *part;
+    TC *CS;
+    int64_t ldcs;
+    double *grp, *rpt;               // rpt null: no fused row statistics
+    int64_t nt;
+    int rmode;
+    const double *rw;
+};
 template <typename TC>
-__global__ __launch_bounds__(kThreads) void k_encode_finish(int64_t b, int64_t k, TC *CS, int64_t ldcs, bool stat,
-                                                            int64_t P, const double *part, double *grp, double *rp,
-                                                            int64_t rps, int64_t R, int rmode, const double *rw) {
-    const int64_t rel = b * k;
-    for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < rel; t += (int64_t)gridDim.x * kThreads) {
-        int64_t r = t / k, l = t - r * k;
-        // four independent running sums (partitions p mod 4) keep eight loads in flight
-        double s4[4] = {0.0, 0.0, 0.0, 0.0}, ss4[4] = {0.0, 0.0, 0.0, 0.0};
-        int64_t p = 0;
-        for (; p + 3 < P; p += 4) {
+__global__ __launch_bounds__(kThreads) void k_encode_finish(FinSide<TC> x, FinSide<TC> y, unsigned na, bool stat) {
+    constexpr int NW = kThreads / kWave;
+    __shared__ double sh[2][NW][kWave];
+    const FinSide<TC> &o = blockIdx.x < na ? x : y;
+    const int64_t idx = blockIdx.x < na ? blockIdx.x : blockIdx.x - na;
+    const int64_t cbs = (o.k + kWave - 1) / kWave, cb = idx % cbs, r = idx / cbs;
+    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+    const int64_t l = cb * kWave + lane, rel = o.b * o.k;
+    const bool ok = l < o.k;
+    double s4[4] = {}, ss4[4] = {};
+    if (ok) {
+        const double *src = o.part + r * o.k + l;
+        int64_t p = w;
+        for (; p + 3 * NW < o.P; p += 4 * NW) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                s4[q] += part[(2 * (p + q)) * rel + t];
-                ss4[q] += part[(2 * (p + q) + 1) * rel + t];
+                s4[q] += src[2 * (p + q * NW) * rel];
+                ss4[q] += src[(2 * (p + q * NW) + 1) * rel];
             }
         }
-        for (int q = 0; p < P; ++p, ++q) {
-            s4[q] += part[(2 * p) * rel + t];
-            ss4[q] += part[(2 * p + 1) * rel + t];
-        }
-        const double sv = (s4[0] + s4[1]) + (s4[2] + s4[3]), ssv = (ss4[0] + ss4[1]) + (ss4[2] + ss4[3]);
-        finish_encode<TC>(sv, ssv, stat, CS + r * ldcs + l, grp + t);
-        if (rp) {
-            const double c = (double)(TC)sv, gv = stat ? ssv + c * c : ssv;
-            row_partial(rp, rps, R + r, l / kWave, row_term(rmode, c, rmode == ROW_W ? rw[l] : 0.0));
-            row_partial(rp, rps, R + b + r, l / kWave, gv * gv);
+        for (int q = 0; p < o.P; p += NW, ++q) {
+            s4[q] += src[2 * p * rel];
+            ss4[q] += src[(2 * p + 1) * rel];
         }
     }
-}
-
-// The fused row statistics from their partials, each row summing its chunks in
-// order: statistic rmode of the R data rows and b checksum rows (out[0 .. R + b);
-// the square root of the sum except for ROW_W) and ||row||_2 of the b
-// group-statistic rows (out_grp).
-__global__ __launch_bounds__(kThreads) void k_rows_finish(const double *rp, int64_t rps, int64_t R, int64_t b,
-                                                          int64_t n_data, int64_t n_tail, int rmode, double *out,
-                                                          double *out_grp) {
-    const int64_t rows = R + 2 * b;
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < rows; i += (int64_t)gridDim.x * kThreads) {
-        const int64_t nc = i < R ? n_data : n_tail;
-        double acc = 0.0;
-        for (int64_t c = 0; c < nc; ++c) acc += rp[i * rps + c];
-        if (i < R + b) out[i] = rmode == ROW_W ? acc : sqrt(acc);
-        else out_grp[i - R - b] = sqrt(acc);
+    sh[0][w][lane] = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+    sh[1][w][lane] = (ss4[0] + ss4[1]) + (ss4[2] + ss4[3]);
+    __syncthreads();
+    if (w) return;
+    const double sv = (sh[0][0][lane] + sh[0][1][lane]) + (sh[0][2][lane] + sh[0][3][lane]);
+    const double ssv = (sh[1][0][lane] + sh[1][1][lane]) + (sh[1][2][lane] + sh[1][3][lane]);
+    if (ok) finish_encode<TC>(sv, ssv, stat, o.CS + r * o.ldcs + l, o.grp + r * o.k + l);
+    if (o.rpt) {
+        const double cs = (double)(TC)sv, gv = stat ? ssv + cs * cs : ssv;
+        const double c2 = wave_sum(ok ? row_term(o.rmode, cs, o.rmode == ROW_W ? o.rw[l] : 0.0) : 0.0);
+        const double g2 = wave_sum(ok ? gv * gv : 0.0);
+        if (lane == 0) {
+            o.rpt[r * o.nt + cb] = c2;
+            o.rpt[(o.b + r) * o.nt + cb] = g2;
+        }
     }
 }
 
@@ -294,7 +381,8 @@ constexpr int kRowThreads = 512;       // 8 waves share one copy of w
 // with the weights in LDS, permuted as above).
 template <typename T, int MODE, bool WLDS>
 __device__ __attribute__((always_inline)) inline void row_stats_rows(const T *X, int64_t ld, int64_t rows, int64_t k,
-                                                                     const double *w, const float *wsh, double *out) {
+                                                                     const double *w, const float *wsh, double *out,
+                                                                     int64_t blk, int64_t nblk) {
     constexpr int V = vec16<T>::N;
     constexpr int NW = kRowThreads / kWave;
     constexpr int64_t CH = (int64_t)kWave * V;
@@ -309,7 +397,7 @@ __device__ __attribute__((always_inline)) inline void row_stats_rows(const T *X,
             else acc += v2;
         }
     };
-    for (int64_t i = (int64_t)blockIdx.x * NW + wave; i < rows; i += (int64_t)gridDim.x * NW) {
+    for (int64_t i = blk * NW + wave; i < rows; i += nblk * NW) {
         const T *row = X + i * ld;
         double acc = 0.0;
         constexpr int64_t step = CH;
@@ -335,111 +423,221 @@ __device__ __attribute__((always_inline)) inline void row_stats_rows(const T *X,
     }
 }
 
+// Everything an encode still owes once the sums are finished, in one launch:
+// a list of jobs, each with its own run of blocks.
+//   JOB_ROWS: statistic `mode` of `rows` rows of X (k columns of T), a wave per row
+//   JOB_TAIL_C / JOB_TAIL_D: the same of checksum rows (TC) / group rows
+//     (double), a block per row: they are few and long
+//   JOB_SUM: rows' statistics from their partials X[row * ld + 0 .. k), eight lanes per row
+//   JOB_ZERO: out[0 .. rows) = 0
+enum { JOB_ROWS, JOB_TAIL_C, JOB_TAIL_D, JOB_SUM, JOB_ZERO };
+struct EncJob {
+    int kind, mode;
+    unsigned blocks;
+    const void *X;
+    int64_t ld, rows, k;
+    const double *w;
+    double *out;
+};
+constexpr int kMaxJobs = 8;
+struct EncJobs {
+    int n;
+    EncJob j[kMaxJobs];
+};
+
 template <typename T>
-__global__ __launch_bounds__(kRowThreads) void k_row_stats(const T *X, int64_t ld, int64_t rows, int64_t k, int mode,
-                                                           const double *w, double *out) {
-    constexpr int64_t CH = (int64_t)kWave * vec16<T>::N;   // columns per chunk (one 16-byte load per lane)
-    extern __shared__ float wsh[];                     // whole chunks of k when mode == ROW_W and k <= kRowWMaxK
-    const bool wlds = mode == ROW_W && k <= kRowWMaxK;
-    if (wlds) {
-        for (int64_t l = threadIdx.x; l < k; l += kRowThreads) {
-            const int64_t c = l / CH, e = l - c * CH;
-            wsh[c * CH + (e % vec16<T>::N) * kWave + e / vec16<T>::N] = (float)w[l];
-        }
-        __syncthreads();
-    }
-    if (mode == ROW_W) {
-        if (wlds) row_stats_rows<T, ROW_W, true>(X, ld, rows, k, w, wsh, out);
-        else row_stats_rows<T, ROW_W, false>(X, ld, rows, k, w, wsh, out);
-    } else if (mode == ROW_L4SQ) {
-        row_stats_rows<T, ROW_L4SQ, false>(X, ld, rows, k, w, wsh, out);
-    } else {
-        row_stats_rows<T, ROW_L2, false>(X, ld, rows, k, w, wsh, out);
-    }
-}
-
-// Row statistics launch: with LDS-staged weights a block serves many rows.
-template <typename T>
-static void row_stats(const T *X, int64_t ld, int64_t rows, int64_t k, int mode, const double *w, double *out,
-                      hipStream_t s) {
-    if (rows <= 0) return;
-    constexpr int NW = kRowThreads / kWave;
-    constexpr int64_t CH = (int64_t)kWave * vec16<T>::N;   // the permuted weights fill whole chunks
-    static_assert(kRowWMaxK % CH == 0, "whole chunks within the LDS limit");
-    size_t lds = (mode == ROW_W && k <= kRowWMaxK) ? sizeof(float) * (size_t)((k + CH - 1) / CH * CH) : 0;
-    unsigned grid = (unsigned)std::min<int64_t>((rows + NW - 1) / NW, lds ? 512 : 65536);
-    k_row_stats<T><<<grid, kRowThreads, lds, s>>>(X, ld, rows, k, mode, w, out);
-}
-
-static unsigned grid_for(int64_t work) { return (unsigned)std::min<int64_t>((work + kThreads - 1) / kThreads, 65536); }
-static unsigned rows_grid(int64_t rows) { return (unsigned)std::min<int64_t>(std::max<int64_t>(rows, 1), 65536); }
-
-// Pass 1 over one operand: checksum rows CS (ldcs) and grp; with rp (k / V a
-// multiple of 64) also the row-statistic partials of the data and checksum rows
-// (statistic rmode, weights rw) and of the group rows, finished into rows_out
-// (R + b) and grp_out (b).
-template <typename T, typename TC, class Src>
-static void encode_pass1(Src src, int64_t R, int64_t b, int64_t k, TC *CS, int64_t ldcs, bool stat, double *grp,
-                         double *part, hipStream_t s, double *rp = nullptr, int rmode = ROW_L2,
-                         const double *rw = nullptr, double *rows_out = nullptr, double *grp_out = nullptr) {
+__device__ inline void tail_row(const EncJob &o, int64_t i) {
+    __shared__ double sh[kRowThreads / kWave];
     constexpr int V = vec16<T>::N;
-    int64_t G = R / b;
-    int64_t P = group_partitions(G, b, k / V);
-    const int64_t rps = k / kWave;                 // partial slots per row (chunks of 64 columns at most)
-    int64_t n_tail;
-    int64_t chunk = 0;
-    if (P > 1) {
-        chunk = (G + P - 1) / P;
-        P = (G + chunk - 1) / chunk;
+    const T *row = (const T *)o.X + i * o.ld;
+    double acc = 0.0;
+    for (int64_t l = (int64_t)threadIdx.x * V; l < o.k; l += kRowThreads * V) {
+        double v[V];
+        vec16<T>::load(row + l, v);
+#pragma unroll
+        for (int q = 0; q < V; ++q) acc += row_term(o.mode, v[q], o.mode == ROW_W ? o.w[l + q] : 0.0);
     }
-    // the statistic modes as template arguments (no per-element selects)
-    auto pass = [&](auto st, auto rm) {
-        constexpr bool ST = decltype(st)::value;
-        constexpr int RM = decltype(rm)::value;
-        if (P == 1)
-            k_encode_direct<T, TC, Src, ST, RM><<<grid_for(b * k / V), kThreads, 0, s>>>(src, b, G, k, CS, ldcs, grp,
-                                                                                         rp, rps, rw);
-        else
-            k_encode_partial<T, Src, ST, RM><<<grid_for(P * b * k / V), kThreads, 0, s>>>(src, b, G, k, P, chunk, part,
-                                                                                          rp, rps, rw);
-    };
-    auto by_row = [&](auto st) {
-        if (!rp) pass(st, std::integral_constant<int, kRowNone>{});
-        else if (rmode == ROW_W) pass(st, std::integral_constant<int, ROW_W>{});
-        else if (rmode == ROW_L4SQ) pass(st, std::integral_constant<int, ROW_L4SQ>{});
-        else pass(st, std::integral_constant<int, ROW_L2>{});
-    };
-    if (stat) by_row(std::true_type{});
-    else by_row(std::false_type{});
-    if (P == 1) {
-        n_tail = k / (kWave * V);
-    } else {
-        k_encode_finish<TC><<<grid_for(b * k), kThreads, 0, s>>>(b, k, CS, ldcs, stat, P, part, grp, rp, rps, R,
-                                                                 rmode, rw);
-        n_tail = k / kWave;
+    acc = wave_sum(acc);
+    if (threadIdx.x % kWave == 0) sh[threadIdx.x / kWave] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < kRowThreads / kWave; ++q) acc += sh[q];
+        o.out[i] = o.mode == ROW_W ? acc : sqrt(acc);
     }
-    if (rp)
-        k_rows_finish<<<grid_for(R + 2 * b), kThreads, 0, s>>>(rp, rps, R, b, k / (kWave * V), n_tail, rmode,
-                                                               rows_out, grp_out);
 }
 
-// Pass 2 over one operand: a statistic per row of the data rows and of the
-// checksum rows.  det: ||row||_2; stat with the other side thin (b_other == 1):
-// sum_l row_l^2 w_l (w = the other side's grp); stat otherwise: ||row||_4^2.
 template <typename T, typename TC>
-static void encode_pass2(const T *X, int64_t ld, int64_t R, const TC *CS, int64_t ldcs, int64_t b, int64_t k,
-                         bool stat, int64_t b_other, const double *w_other, double *out, hipStream_t s) {
-    int mode = !stat ? ROW_L2 : (b_other == 1 ? ROW_W : ROW_L4SQ);
-    row_stats<T>(X, ld, R, k, mode, w_other, out, s);
-    row_stats<TC>(CS, ldcs, b, k, mode, w_other, out + R, s);
+__global__ __launch_bounds__(kRowThreads) void k_encode_jobs(EncJobs jobs) {
+    constexpr int64_t CH = (int64_t)kWave * vec16<T>::N;   // columns per chunk (one 16-byte load per lane)
+    extern __shared__ float wsh[];                     // whole chunks of k for a ROW_W job with k <= kRowWMaxK
+    int64_t blk = blockIdx.x;
+    int q = 0;
+    while (q + 1 < jobs.n && blk >= jobs.j[q].blocks) blk -= jobs.j[q++].blocks;
+    const EncJob &o = jobs.j[q];
+    switch (o.kind) {
+    case JOB_ROWS: {
+        const T *X = (const T *)o.X;
+        if (o.mode == ROW_W && o.k <= kRowWMaxK) {
+            for (int64_t l = threadIdx.x; l < o.k; l += kRowThreads) {
+                const int64_t c = l / CH, e = l - c * CH;
+                wsh[c * CH + (e % vec16<T>::N) * kWave + e / vec16<T>::N] = (float)o.w[l];
+            }
+            __syncthreads();
+            row_stats_rows<T, ROW_W, true>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
+        } else if (o.mode == ROW_W) {
+            row_stats_rows<T, ROW_W, false>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
+        } else if (o.mode == ROW_L4SQ) {
+            row_stats_rows<T, ROW_L4SQ, false>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
+        } else {
+            row_stats_rows<T, ROW_L2, false>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
+        }
+        break;
+    }
+    case JOB_TAIL_C: tail_row<TC>(o, blk); break;
+    case JOB_TAIL_D: tail_row<double>(o, blk); break;
+    case JOB_SUM: {
+        const int64_t i = blk * (kRowThreads / 8) + threadIdx.x / 8;
+        if (i >= o.rows) break;
+        const double *x = (const double *)o.X + i * o.ld;
+        double acc = 0.0;
+        for (int64_t c = threadIdx.x % 8; c < o.k; c += 8) acc += x[c];
+        acc += __shfl_xor(acc, 4);
+        acc += __shfl_xor(acc, 2);
+        acc += __shfl_xor(acc, 1);
+        if (threadIdx.x % 8 == 0) o.out[i] = o.mode == ROW_W ? acc : sqrt(acc);
+        break;
+    }
+    default:
+        for (int64_t t = blk * kRowThreads + threadIdx.x; t < o.rows; t += (int64_t)o.blocks * kRowThreads) o.out[t] = 0.0;
+        break;
+    }
 }
 
-template <typename T, typename TC, class SrcA, class SrcB>
-static int encode_typed(const abft_problem *p, SrcA srcA, SrcB srcB, T *A, T *Bt, TC *Acs, int64_t ldacs, TC *Bcs,
+// The job list of one launch.
+struct JobList {
+    EncJobs a{};
+    size_t lds = 0;
+    unsigned blocks = 0;
+    void add(int kind, int mode, int64_t nblk, const void *X, int64_t ld, int64_t rows, int64_t k, const double *w,
+             double *out) {
+        if (rows <= 0) return;
+        a.j[a.n++] = EncJob{kind, mode, (unsigned)nblk, X, ld, rows, k, w, out};
+        blocks += (unsigned)nblk;
+    }
+    // With LDS-staged weights a block serves many rows.
+    template <typename T> void rows(const T *X, int64_t ld, int64_t rows, int64_t k, int mode, const double *w,
+                                    double *out) {
+        constexpr int NW = kRowThreads / kWave;
+        constexpr int64_t CH = (int64_t)kWave * vec16<T>::N;   // the permuted weights fill whole chunks
+        static_assert(kRowWMaxK % CH == 0, "whole chunks within the LDS limit");
+        const bool wlds = mode == ROW_W && k <= kRowWMaxK;
+        if (wlds) lds = std::max(lds, sizeof(float) * (size_t)((k + CH - 1) / CH * CH));
+        add(JOB_ROWS, mode, std::min<int64_t>((rows + NW - 1) / NW, wlds ? 512 : 65536), X, ld, rows, k, w, out);
+    }
+    void sums(const double *X, int64_t ld, int64_t rows, int64_t n, int mode, double *out) {
+        add(JOB_SUM, mode, (rows + kRowThreads / 8 - 1) / (kRowThreads / 8), X, ld, rows, n, nullptr, out);
+    }
+    void zero(double *out, int64_t n) {
+        add(JOB_ZERO, 0, std::min<int64_t>((n + kRowThreads - 1) / kRowThreads, 64), nullptr, 0, n, 0, nullptr, out);
+    }
+    template <typename T, typename TC> void launch(hipStream_t s) {
+        if (blocks) k_encode_jobs<T, TC><<<blocks, kRowThreads, lds, s>>>(a);
+    }
+};
+
+// One side of the encode pass: its split, buffers and statistics.
+template <class Src, typename TC> struct EncJobSide {
+    EncSide<Src, TC> o;
+    EncSplit sp;
+    int rmode;
+    double *rows_out, *grp_out;      // statistic of the R + b rows, norms of the group rows
+    bool fused;                      // row statistics from the pass's partials
+    int64_t R;
+};
+template <class Src, typename TC>
+static EncJobSide<Src, TC> enc_side(Src src, int64_t R, int64_t b, int64_t k, TC *CS, int64_t ldcs, double *grp,
+                                    double *part, double *rowpart, bool fused, int rmode, const double *rw,
+                                    double *rows_out, double *grp_out) {
+    EncJobSide<Src, TC> x;
+    x.sp = enc_split(R, b, k, Src::V);
+    x.R = R;
+    x.rmode = rmode;
+    x.fused = fused;
+    x.rows_out = rows_out;
+    x.grp_out = grp_out;
+    x.o = EncSide<Src, TC>{src, b, R / b, k, x.sp.strips, x.sp.P, x.sp.chunk, part, CS, ldcs, grp, rowpart,
+                           rowpart + R * x.sp.strips, x.sp.tail_slots, rw};
+    return x;
+}
+
+// The pass over one side (y null) or both in one launch (the same split form
+// and statistic), then the finish of the partitioned sums.
+template <class Src, typename TC>
+static void enc_launch(const EncJobSide<Src, TC> &x, const EncJobSide<Src, TC> *y, bool stat, hipStream_t s) {
+    auto pass = [&](auto cw, auto st, auto rm, const EncJobSide<Src, TC> &u, const EncJobSide<Src, TC> *v) {
+        constexpr int CW = decltype(cw)::value, RM = decltype(rm)::value;
+        constexpr bool ST = decltype(st)::value;
+        const EncSide<Src, TC> &vo = v ? v->o : u.o;
+        const int64_t nb = v ? v->sp.blocks : 0;
+        if (u.sp.direct)
+            k_encode_direct<CW, Src, TC, ST, RM><<<(unsigned)(u.sp.blocks + nb), kThreads, 0, s>>>(
+                u.o, vo, (unsigned)u.sp.blocks);
+        else
+            k_encode_partial<CW, Src, TC, ST, RM><<<(unsigned)(u.sp.blocks + nb), kThreads, 0, s>>>(
+                u.o, vo, (unsigned)u.sp.blocks);
+    };
+    auto by_mode = [&](const EncJobSide<Src, TC> &u, const EncJobSide<Src, TC> *v) {
+        const int rm = u.fused ? u.rmode : kRowNone;
+        auto by_rm = [&](auto cw, auto st) {
+            if (rm == kRowNone) pass(cw, st, std::integral_constant<int, kRowNone>{}, u, v);
+            else if constexpr (!decltype(st)::value) pass(cw, st, std::integral_constant<int, ROW_L2>{}, u, v);
+            else if (rm == ROW_W) pass(cw, st, std::integral_constant<int, ROW_W>{}, u, v);
+            else pass(cw, st, std::integral_constant<int, ROW_L4SQ>{}, u, v);
+        };
+        auto by_stat = [&](auto cw) {
+            if (stat) by_rm(cw, std::true_type{});
+            else by_rm(cw, std::false_type{});
+        };
+        if (u.sp.cw == 64) by_stat(std::integral_constant<int, 64>{});
+        else by_stat(std::integral_constant<int, 16>{});
+    };
+    const bool one = y && x.sp.direct == y->sp.direct && x.sp.cw == y->sp.cw && x.fused == y->fused &&
+                     (!x.fused || x.rmode == y->rmode);
+    by_mode(x, one ? y : nullptr);
+    if (y && !one) by_mode(*y, nullptr);
+    auto fin = [](const EncJobSide<Src, TC> &u) {
+        return FinSide<TC>{u.o.b, u.o.k, u.o.P, u.o.part, u.o.CS, u.o.ldcs, u.o.grp, u.fused ? u.o.rpt : nullptr,
+                           u.o.nt, u.rmode, u.o.rw};
+    };
+    auto nfin = [](const EncJobSide<Src, TC> *u) {
+        return u && !u->sp.direct ? (unsigned)(u->o.b * ((u->o.k + kWave - 1) / kWave)) : 0u;
+    };
+    const unsigned nx = nfin(&x), ny = nfin(y);
+    if (nx + ny) k_encode_finish<TC><<<nx + ny, kThreads, 0, s>>>(fin(x), fin(y ? *y : x), nx, stat);
+}
+
+// Row statistics of one side: sums of the pass's partials, or a pass of their
+// own over the stored operand and the checksum and group rows.
+template <typename T, class Src, typename TC>
+static void enc_rows_jobs(JobList &jl, const EncJobSide<Src, TC> &x, const T *X, int64_t ld) {
+    const EncSide<Src, TC> &o = x.o;
+    if (x.fused) {
+        const int64_t nt = x.sp.direct ? x.sp.strips : (o.k + kWave - 1) / kWave;
+        jl.sums(o.rp, o.strips, x.R, o.strips, x.rmode, x.rows_out);
+        jl.sums(o.rpt, o.nt, o.b, nt, x.rmode, x.rows_out + x.R);
+        jl.sums(o.rpt + o.b * o.nt, o.nt, o.b, nt, ROW_L2, x.grp_out);
+    } else {
+        jl.rows<T>(X, ld, x.R, o.k, x.rmode, o.rw, x.rows_out);
+        jl.add(JOB_TAIL_C, x.rmode, o.b, o.CS, o.ldcs, o.b, o.k, o.rw, x.rows_out + x.R);
+        jl.add(JOB_TAIL_D, ROW_L2, o.b, o.grp, o.k, o.b, o.k, nullptr, x.grp_out);
+    }
+}
+
+template <typename T, typename TC, class Src>
+static int encode_typed(const abft_problem *p, Src srcA, Src srcB, T *A, T *Bt, TC *Acs, int64_t ldacs, TC *Bcs,
                         int64_t ldbcs, char *ws, hipStream_t s) {
     Geom g = geom_of(p);
     WsLayout L = ws_layout(p);
-    double *part = (double *)(ws + L.partial);
     double *grpA = (double *)(ws + L.grpA), *grpB = (double *)(ws + L.grpB);
     const bool stat = p->tau_mode == ABFT_TAU_STAT;
     // row statistics (det: na, nb; stat: qr, qc) and the norms of the grp rows
@@ -450,25 +648,29 @@ static int encode_typed(const abft_problem *p, SrcA srcA, SrcB srcB, T *A, T *Bt
     // otherwise: ||row||_4^2
     const int modeA = !stat ? ROW_L2 : (g.bc == 1 ? ROW_W : ROW_L4SQ);
     const int modeB = !stat ? ROW_L2 : (g.br == 1 ? ROW_W : ROW_L4SQ);
-    // With rows_fused the encode pass produces the row statistics too (no second read of the operand),
-    // except A's sum_l A_il^2 w_l, whose weights (B's grp) exist only after B's encode.
-    double *rp = rows_fused(p) ? (double *)(ws + L.rowpart) : nullptr;
-    const bool fuseA = rp && modeA != ROW_W, fuseB = rp != nullptr;
-    encode_pass1<T, TC>(srcA, g.m, g.br, g.k, Acs, ldacs, stat, grpA, part, s, fuseA ? rp : nullptr, modeA, nullptr,
-                        ra, ga);
-    encode_pass1<T, TC>(srcB, g.n, g.bc, g.k, Bcs, ldbcs, stat, grpB, part, s, fuseB ? rp : nullptr, modeB, grpA, rb,
-                        gb);
-    if (!fuseA) {
-        encode_pass2<T, TC>(A, p->lda, g.m, Acs, ldacs, g.br, g.k, stat, g.bc, grpB, ra, s);
-        row_stats<double>(grpA, g.k, g.br, g.k, ROW_L2, nullptr, ga, s);
+    // The pass produces the row statistics too, unless their weights do not exist yet: A's weights are B's
+    // grp and B's are A's.  B's can still be fused by running A's pass first, in launches of their own; that
+    // saves reading B again and costs two launches and the overlap of the two passes, so it pays from about
+    // kEncRereadBytes of B on (a re-read at 5 TB/s against 10 us).
+    const bool serial = modeB == ROW_W && g.n * g.k * (int64_t)sizeof(T) > kEncRereadBytes;
+    const bool fuseA = modeA != ROW_W, fuseB = modeB != ROW_W || serial;
+    auto a = enc_side<Src, TC>(srcA, g.m, g.br, g.k, Acs, ldacs, grpA, (double *)(ws + L.partial),
+                                (double *)(ws + L.rowpart), fuseA, modeA, grpB, ra, ga);
+    auto b = enc_side<Src, TC>(srcB, g.n, g.bc, g.k, Bcs, ldbcs, grpB, (double *)(ws + L.partial_b),
+                                (double *)(ws + L.rowpart_b), fuseB, modeB, grpA, rb, gb);
+    if (serial) {
+        enc_launch<Src, TC>(a, nullptr, stat, s);
+        enc_launch<Src, TC>(b, nullptr, stat, s);
+    } else {
+        enc_launch<Src, TC>(a, &b, stat, s);
     }
-    if (!fuseB) {
-        encode_pass2<T, TC>(Bt, p->ldb, g.n, Bcs, ldbcs, g.bc, g.k, stat, g.br, grpA, rb, s);
-        row_stats<double>(grpB, g.k, g.bc, g.k, ROW_L2, nullptr, gb, s);
-    }
+    JobList jl;
+    enc_rows_jobs<T>(jl, a, A, p->lda);
+    enc_rows_jobs<T>(jl, b, Bt, p->ldb);
     // an operand encoded here carries no inherited residual
-    k_fill_zero<<<1, kThreads, 0, s>>>((double *)(ws + L.chain_a), g.br);
-    k_fill_zero<<<1, kThreads, 0, s>>>((double *)(ws + L.chain_w), g.N);
+    jl.zero((double *)(ws + L.chain_a), g.br);
+    jl.zero((double *)(ws + L.chain_w), g.N);
+    jl.launch<T, TC>(s);
     ABFT_LAUNCHED();
     return ABFT_OK;
 }
@@ -515,19 +717,23 @@ static int encode_chained_typed(const abft_problem *p, const T *A, T *Bt, char *
                                 const char *ws_prev, double cc_prev, hipStream_t s) {
     Geom g = geom_of(p);
     WsLayout L = ws_layout(p), Lp = ws_layout(prev);
-    double *part = (double *)(ws + L.partial);
     double *grpA = (double *)(ws + L.grpA), *grpB = (double *)(ws + L.grpB);
-    T *cs = (T *)(ws + L.chain_cs);
-    // the A side: group statistic (checksum rows into scratch), row norms of the rows that enter the product
-    encode_pass1<T, T>(SrcStored<T>{A, p->lda}, g.m, g.br, g.k, cs, g.k, false, grpA, part, s);
-    encode_pass2<T, T>(A, p->lda, g.m, A + g.m * p->lda, p->lda, g.br, g.k, false, g.bc, grpB, (double *)(ws + L.na),
-                       s);
-    // the B side as in a plain encode
-    encode_pass1<T, T>(SrcStored<T>{Bt, p->ldb}, g.n, g.bc, g.k, Bt + g.n * p->ldb, p->ldb, false, grpB, part, s);
-    encode_pass2<T, T>(Bt, p->ldb, g.n, Bt + g.n * p->ldb, p->ldb, g.bc, g.k, false, g.br, grpA,
-                       (double *)(ws + L.nb), s);
-    row_stats<double>(grpA, g.k, g.br, g.k, ROW_L2, nullptr, (double *)(ws + L.na_abs), s);
-    row_stats<double>(grpB, g.k, g.bc, g.k, ROW_L2, nullptr, (double *)(ws + L.nb_abs), s);
+    typedef SrcStored<T> Src;
+    // the A side: group statistic (checksum rows into scratch); the B side as in a plain encode
+    auto a = enc_side<Src, T>(Src{A, p->lda}, g.m, g.br, g.k, (T *)(ws + L.chain_cs), g.k, grpA,
+                              (double *)(ws + L.partial), (double *)(ws + L.rowpart), false, ROW_L2, nullptr, nullptr,
+                              nullptr);
+    auto b = enc_side<Src, T>(Src{Bt, p->ldb}, g.n, g.bc, g.k, Bt + g.n * p->ldb, p->ldb, grpB,
+                              (double *)(ws + L.partial_b), (double *)(ws + L.rowpart_b), false, ROW_L2, nullptr,
+                              nullptr, nullptr);
+    enc_launch<Src, T>(a, &b, false, s);
+    // row norms of the rows that enter the product (A's carried rows as they are), norms of the group rows
+    JobList jl;
+    jl.rows<T>(A, p->lda, g.M, g.k, ROW_L2, nullptr, (double *)(ws + L.na));
+    jl.rows<T>(Bt, p->ldb, g.N, g.k, ROW_L2, nullptr, (double *)(ws + L.nb));
+    jl.add(JOB_TAIL_D, ROW_L2, g.br, grpA, g.k, g.br, g.k, nullptr, (double *)(ws + L.na_abs));
+    jl.add(JOB_TAIL_D, ROW_L2, g.bc, grpB, g.k, g.bc, g.k, nullptr, (double *)(ws + L.nb_abs));
+    jl.launch<T, T>(s);
     // the inherited term
     k_chain_a<<<1, kThreads, 0, s>>>((const double *)(ws_prev + Lp.na_abs), cc_prev, g.br, (double *)(ws + L.chain_a));
     k_row_absdot<T><<<(unsigned)std::min<int64_t>((g.N + 3) / 4, 65536), kThreads, 0, s>>>(
@@ -574,6 +780,8 @@ int launch_encode(const abft_problem *p, void *A_f, void *B_f, char *ws, hipStre
         return ABFT_E_UNSUPPORTED;
     }
 }
+
+static unsigned grid_for(int64_t work) { return (unsigned)std::min<int64_t>((work + kThreads - 1) / kThreads, 65536); }
 
 // ------------------------------------------------------------------ quantize
 // binary32 -> bfloat16, round to nearest even; 8 values per thread and step.
