@@ -69,6 +69,7 @@ WsLayout ws_layout(const abft_problem *p) {
     L.acs = take(cs_in_ws(p->dtype) ? sizeof(float) * g.br * g.k : 8);
     L.bcs = take(cs_in_ws(p->dtype) ? sizeof(float) * g.bc * g.k : 8);
     L.scale = take(16);
+    L.amax = take(p->dtype == ABFT_FP8_E4M3 ? sizeof(float) * 2 * kAmaxBlocks : 8);
     // partial sums: encode A (2 stats), encode B (2 stats), verify columns (1, in A's)
     const EncSplit ea = enc_split(g.m, g.br, g.k, enc_vec(p->dtype)), eb = enc_split(g.n, g.bc, g.k, enc_vec(p->dtype));
     int64_t pc = std::max(group_partitions(g.Gr, g.br, g.N), group_partitions(g.Gr, g.br, (g.N + 1) / 2));

@@ -67,6 +67,18 @@ __host__ __device__ inline uint8_t f32_to_e4m3_rne(float x) {
     return sign | (uint8_t)code;
 }
 
+// Four binary32 values to E4M3 bytes by the conversion instruction (round to
+// nearest even, subnormals included).  Values are clamped to +-448 first, so
+// every |x| > 448 gives +-448 as in f32_to_e4m3_rne; a NaN passes, and its
+// byte's sign (the instruction may set it) is cleared.  The same code as
+// f32_to_e4m3_rne for every binary32 pattern up to 448, infinities and NaN.
+__device__ inline uint32_t f32x4_to_e4m3(float a, float b, float c, float d) {
+    auto sat = [](float x) { return x != x ? x : fminf(fmaxf(x, -448.0f), 448.0f); };
+    int w = __builtin_amdgcn_cvt_pk_fp8_f32(sat(a), sat(b), 0, false);
+    const uint32_t u = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(sat(c), sat(d), w, true);
+    return u & ~(((u & 0x7F7F7F7Fu) + 0x01010101u) & 0x80808080u);
+}
+
 template <typename T> struct elem;
 template <> struct elem<double> {
     __device__ static double load(const double *p) { return *p; }
@@ -208,7 +220,8 @@ struct WsLayout {
     size_t qr, qc, nv, nw;           // stat statistics (double)
     size_t grpA, grpB;               // per-residue group sums of |A| (or A^2) and of |B| (double, br*k / bc*k)
     size_t acs, bcs;                 // binary32 checksum rows of low-precision operands (float, br*k / bc*k)
-    size_t scale;                    // FP8 per-tensor scale exponents and amax scratch (4 x int32)
+    size_t scale;                    // FP8 per-tensor scale exponents and amax (4 x int32)
+    size_t amax;                     // FP8: the amax pass's maximum per block (2 x kAmaxBlocks floats)
     size_t partial, partial_b;       // two-level reduction partials (double): A's encode and the verification; B's encode
     size_t fused_c, fused_r;         // product-epilogue partial sums for b = 1 (double)
     size_t chain_a, chain_w;         // chained products: inherited threshold term chain_a[r] chain_w[j]
@@ -240,6 +253,9 @@ struct EncSplit {
 EncSplit enc_split(int64_t R, int64_t b, int64_t k, int V);
 // B's size from which its row statistics are worth a serial pass (see encode_typed).
 constexpr int64_t kEncRereadBytes = int64_t(48) << 20;
+
+// Blocks per operand of the FP8 amax pass: eight per CU.
+constexpr int64_t kAmaxBlocks = 2048;
 
 // Number of partitions used for the row-group sums of a (G groups, b residues, cols) sum.
 int64_t group_partitions(int64_t G, int64_t b, int64_t cols);

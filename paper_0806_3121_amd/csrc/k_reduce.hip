@@ -102,17 +102,34 @@ __device__ inline double row_term(int mode, double x, double w) {
     return mode == ROW_W ? x2 * w : (mode == ROW_L4SQ ? x2 * x2 : x2);
 }
 
+// Streaming (non-temporal) access: a pass over data far larger than the caches
+// is faster with it -- the FP8 scale's read of two 8192 x 8192 binary32
+// operands 107 -> 81 us (6.6 TB/s), the binary64 encode of two 8192 x 8192
+// operands 263 -> 243, the bfloat16 values stored by the quantizing pass over a
+// 16384 x 16384 operand 341 -> 319 -- while data that fits the 256 MB
+// memory-side cache is left there for the pass or the product that reads it next.
+// The quantizing passes' own loads gain nothing from it (FP8: 62 -> 67 us, the
+// scale's read leaves part of the operand in that cache).
+static bool streams(int64_t bytes) { return bytes > (int64_t(256) << 20); }
+static bool operands_stream(const abft_problem *p) {
+    return streams((p->m + p->n) * p->k * (int64_t)dtype_size(p->dtype));
+}
+template <bool NT, typename R> __device__ inline R load_raw(const void *p) {
+    if constexpr (NT) return __builtin_nontemporal_load((const R *)p);
+    else return *(const R *)p;
+}
+
 // Where the encode pass takes an operand's values from: the stored operand,
 // or binary32 values quantized to bfloat16 on the way (round to nearest even),
 // which are written to the operand's storage and used as stored.  fetch
 // requests the V values X[row, l0 .. l0+V) (raw words, so that several rows
 // are in flight), take fills them in as binary64.
-template <typename T> struct SrcStored {
+template <typename T, bool NT> struct SrcStored {
     static constexpr int V = kEncVec<T>;
     typedef typename std::conditional<V * sizeof(T) == 16, v4u32, uint64_t>::type Raw;
     const T *X;
     int64_t ld;
-    __device__ Raw fetch(int64_t row, int64_t l0) const { return *(const Raw *)(X + row * ld + l0); }
+    __device__ Raw fetch(int64_t row, int64_t l0) const { return load_raw<NT, Raw>(X + row * ld + l0); }
     __device__ void take(const Raw &w, int64_t, int64_t, double *v) const {
         if constexpr (V * sizeof(T) == 16) {
             vec16<T>::widen(w, v);
@@ -123,7 +140,7 @@ template <typename T> struct SrcStored {
         }
     }
 };
-struct SrcQuantBf16 {
+template <bool NT> struct SrcQuantBf16 {
     static constexpr int V = kEncVec<uint16_t>;
     typedef float v4 __attribute__((ext_vector_type(4)));
     struct Raw { v4 x0, x1; };
@@ -132,7 +149,8 @@ struct SrcQuantBf16 {
     uint16_t *Q;
     int64_t ldq;
     __device__ Raw fetch(int64_t row, int64_t l0) const {
-        return Raw{*(const v4 *)(X + row * ldx + l0), *(const v4 *)(X + row * ldx + l0 + 4)};
+        const v4 *x = (const v4 *)(X + row * ldx + l0);
+        return Raw{x[0], x[1]};
     }
     __device__ void take(const Raw &w, int64_t row, int64_t l0, double *v) const {
         uint16_t h[8];
@@ -144,9 +162,35 @@ struct SrcQuantBf16 {
         v4u32 o;
 #pragma unroll
         for (int q = 0; q < 4; ++q) o[q] = (uint32_t)h[2 * q] | ((uint32_t)h[2 * q + 1] << 16);
-        *(v4u32 *)(Q + row * ldq + l0) = o;
+        if constexpr (NT) __builtin_nontemporal_store(o, (v4u32 *)(Q + row * ldq + l0));
+        else *(v4u32 *)(Q + row * ldq + l0) = o;
 #pragma unroll
         for (int q = 0; q < 8; ++q) v[q] = (double)bf16_to_f32(h[q]);
+    }
+};
+
+// The same to E4M3 under the operand's scale exponent (written by k_scale_exp before the pass).
+struct SrcQuantFp8 {
+    static constexpr int V = kEncVec<uint8_t>;
+    typedef float v4 __attribute__((ext_vector_type(4)));
+    struct Raw { v4 x0, x1; };
+    const float *X;
+    int64_t ldx;
+    uint8_t *Q;
+    int64_t ldq;
+    const int *scale_exp;            // this operand's exponent
+    __device__ Raw fetch(int64_t row, int64_t l0) const {
+        const v4 *x = (const v4 *)(X + row * ldx + l0);
+        return Raw{x[0], x[1]};
+    }
+    __device__ void take(const Raw &w, int64_t row, int64_t l0, double *v) const {
+        const int e = *scale_exp;
+        auto sc = [e](float x) { return __builtin_ldexpf(x, e); };
+        const uint32_t lo = f32x4_to_e4m3(sc(w.x0[0]), sc(w.x0[1]), sc(w.x0[2]), sc(w.x0[3]));
+        const uint32_t hi = f32x4_to_e4m3(sc(w.x1[0]), sc(w.x1[1]), sc(w.x1[2]), sc(w.x1[3]));
+        *(uint64_t *)(Q + row * ldq + l0) = (uint64_t)lo | ((uint64_t)hi << 32);
+        e4m3x4_to_f64(lo, v);
+        e4m3x4_to_f64(hi, v + 4);
     }
 };
 
@@ -379,7 +423,7 @@ constexpr int64_t kRowWMaxK = 16384;   // ROW_W keeps w (as binary32, 64 KB) in 
 constexpr int kRowThreads = 512;       // 8 waves share one copy of w
 // The rows of one block for a statistic fixed at compile time (WLDS: ROW_W
 // with the weights in LDS, permuted as above).
-template <typename T, int MODE, bool WLDS>
+template <typename T, int MODE, bool WLDS, bool NT>
 __device__ __attribute__((always_inline)) inline void row_stats_rows(const T *X, int64_t ld, int64_t rows, int64_t k,
                                                                      const double *w, const float *wsh, double *out,
                                                                      int64_t blk, int64_t nblk) {
@@ -405,7 +449,7 @@ __device__ __attribute__((always_inline)) inline void row_stats_rows(const T *X,
         for (; l0 + 7 * step < k; l0 += 8 * step) {
             v4u32 raw[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) raw[u] = *(const v4u32 *)(row + l0 + u * step);
+            for (int u = 0; u < 8; ++u) raw[u] = load_raw<NT, v4u32>(row + l0 + u * step);
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 double v[V];
@@ -466,7 +510,7 @@ __device__ inline void tail_row(const EncJob &o, int64_t i) {
     }
 }
 
-template <typename T, typename TC>
+template <typename T, typename TC, bool NT>
 __global__ __launch_bounds__(kRowThreads) void k_encode_jobs(EncJobs jobs) {
     constexpr int64_t CH = (int64_t)kWave * vec16<T>::N;   // columns per chunk (one 16-byte load per lane)
     extern __shared__ float wsh[];                     // whole chunks of k for a ROW_W job with k <= kRowWMaxK
@@ -483,13 +527,13 @@ __global__ __launch_bounds__(kRowThreads) void k_encode_jobs(EncJobs jobs) {
                 wsh[c * CH + (e % vec16<T>::N) * kWave + e / vec16<T>::N] = (float)o.w[l];
             }
             __syncthreads();
-            row_stats_rows<T, ROW_W, true>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
+            row_stats_rows<T, ROW_W, true, NT>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
         } else if (o.mode == ROW_W) {
-            row_stats_rows<T, ROW_W, false>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
+            row_stats_rows<T, ROW_W, false, NT>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
         } else if (o.mode == ROW_L4SQ) {
-            row_stats_rows<T, ROW_L4SQ, false>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
+            row_stats_rows<T, ROW_L4SQ, false, NT>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
         } else {
-            row_stats_rows<T, ROW_L2, false>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
+            row_stats_rows<T, ROW_L2, false, NT>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
         }
         break;
     }
@@ -540,8 +584,10 @@ struct JobList {
     void zero(double *out, int64_t n) {
         add(JOB_ZERO, 0, std::min<int64_t>((n + kRowThreads - 1) / kRowThreads, 64), nullptr, 0, n, 0, nullptr, out);
     }
-    template <typename T, typename TC> void launch(hipStream_t s) {
-        if (blocks) k_encode_jobs<T, TC><<<blocks, kRowThreads, lds, s>>>(a);
+    template <typename T, typename TC> void launch(bool nt, hipStream_t s) {
+        if (!blocks) return;
+        if (nt) k_encode_jobs<T, TC, true><<<blocks, kRowThreads, lds, s>>>(a);
+        else k_encode_jobs<T, TC, false><<<blocks, kRowThreads, lds, s>>>(a);
     }
 };
 
@@ -670,7 +716,7 @@ static int encode_typed(const abft_problem *p, Src srcA, Src srcB, T *A, T *Bt, 
     // an operand encoded here carries no inherited residual
     jl.zero((double *)(ws + L.chain_a), g.br);
     jl.zero((double *)(ws + L.chain_w), g.N);
-    jl.launch<T, TC>(s);
+    jl.launch<T, TC>(operands_stream(p), s);
     ABFT_LAUNCHED();
     return ABFT_OK;
 }
@@ -718,7 +764,7 @@ static int encode_chained_typed(const abft_problem *p, const T *A, T *Bt, char *
     Geom g = geom_of(p);
     WsLayout L = ws_layout(p), Lp = ws_layout(prev);
     double *grpA = (double *)(ws + L.grpA), *grpB = (double *)(ws + L.grpB);
-    typedef SrcStored<T> Src;
+    typedef SrcStored<T, false> Src;
     // the A side: group statistic (checksum rows into scratch); the B side as in a plain encode
     auto a = enc_side<Src, T>(Src{A, p->lda}, g.m, g.br, g.k, (T *)(ws + L.chain_cs), g.k, grpA,
                               (double *)(ws + L.partial), (double *)(ws + L.rowpart), false, ROW_L2, nullptr, nullptr,
@@ -733,7 +779,7 @@ static int encode_chained_typed(const abft_problem *p, const T *A, T *Bt, char *
     jl.rows<T>(Bt, p->ldb, g.N, g.k, ROW_L2, nullptr, (double *)(ws + L.nb));
     jl.add(JOB_TAIL_D, ROW_L2, g.br, grpA, g.k, g.br, g.k, nullptr, (double *)(ws + L.na_abs));
     jl.add(JOB_TAIL_D, ROW_L2, g.bc, grpB, g.k, g.bc, g.k, nullptr, (double *)(ws + L.nb_abs));
-    jl.launch<T, T>(s);
+    jl.launch<T, T>(operands_stream(p), s);
     // the inherited term
     k_chain_a<<<1, kThreads, 0, s>>>((const double *)(ws_prev + Lp.na_abs), cc_prev, g.br, (double *)(ws + L.chain_a));
     k_row_absdot<T><<<(unsigned)std::min<int64_t>((g.N + 3) / 4, 65536), kThreads, 0, s>>>(
@@ -749,36 +795,33 @@ int launch_encode_chained(const abft_problem *p, const void *A_f, void *B_f, cha
     return encode_chained_typed(p, (const double *)A_f, (double *)B_f, ws, prev, ws_prev, cc_prev, s);
 }
 
+// Operands already stored as T: checksum rows after the data rows, or (low
+// precision: E4M3 in the scaled domain) binary32 checksum rows in the workspace.
+template <typename T, typename TC, bool NT>
+static int encode_stored(const abft_problem *p, void *A_f, void *B_f, char *ws, hipStream_t s) {
+    const Geom g = geom_of(p);
+    T *A = (T *)A_f, *Bt = (T *)B_f;
+    const SrcStored<T, NT> a{A, p->lda}, b{Bt, p->ldb};
+    if constexpr (std::is_same<T, TC>::value) {
+        return encode_typed<T, TC>(p, a, b, A, Bt, A + g.m * p->lda, p->lda, Bt + g.n * p->ldb, p->ldb, ws, s);
+    } else {
+        const WsLayout L = ws_layout(p);
+        return encode_typed<T, TC>(p, a, b, A, Bt, (TC *)(ws + L.acs), g.k, (TC *)(ws + L.bcs), g.k, ws, s);
+    }
+}
+
 int launch_encode(const abft_problem *p, void *A_f, void *B_f, char *ws, hipStream_t s) {
-    Geom g = geom_of(p);
-    switch (p->dtype) {
-    case ABFT_F64: {
-        double *A = (double *)A_f, *Bt = (double *)B_f;
-        return encode_typed<double, double>(p, SrcStored<double>{A, p->lda}, SrcStored<double>{Bt, p->ldb}, A, Bt,
-                                            A + g.m * p->lda, p->lda, Bt + g.n * p->ldb, p->ldb, ws, s);
-    }
-    case ABFT_F32: {
-        float *A = (float *)A_f, *Bt = (float *)B_f;
-        return encode_typed<float, float>(p, SrcStored<float>{A, p->lda}, SrcStored<float>{Bt, p->ldb}, A, Bt,
-                                          A + g.m * p->lda, p->lda, Bt + g.n * p->ldb, p->ldb, ws, s);
-    }
-    case ABFT_BF16: {
-        // bfloat16 data, binary32 checksum rows in the workspace
-        WsLayout L = ws_layout(p);
-        uint16_t *A = (uint16_t *)A_f, *Bt = (uint16_t *)B_f;
-        return encode_typed<uint16_t, float>(p, SrcStored<uint16_t>{A, p->lda}, SrcStored<uint16_t>{Bt, p->ldb}, A,
-                                             Bt, (float *)(ws + L.acs), g.k, (float *)(ws + L.bcs), g.k, ws, s);
-    }
-    case ABFT_FP8_E4M3: {
-        // E4M3 data (scaled domain), binary32 checksum rows in the workspace
-        WsLayout L = ws_layout(p);
-        uint8_t *A = (uint8_t *)A_f, *Bt = (uint8_t *)B_f;
-        return encode_typed<uint8_t, float>(p, SrcStored<uint8_t>{A, p->lda}, SrcStored<uint8_t>{Bt, p->ldb}, A, Bt,
-                                            (float *)(ws + L.acs), g.k, (float *)(ws + L.bcs), g.k, ws, s);
-    }
-    default:
-        return ABFT_E_UNSUPPORTED;
-    }
+    auto run = [&](auto nt) {
+        constexpr bool NT = decltype(nt)::value;
+        switch (p->dtype) {
+        case ABFT_F64: return encode_stored<double, double, NT>(p, A_f, B_f, ws, s);
+        case ABFT_F32: return encode_stored<float, float, NT>(p, A_f, B_f, ws, s);
+        case ABFT_BF16: return encode_stored<uint16_t, float, NT>(p, A_f, B_f, ws, s);
+        case ABFT_FP8_E4M3: return encode_stored<uint8_t, float, NT>(p, A_f, B_f, ws, s);
+        default: return (int)ABFT_E_UNSUPPORTED;
+        }
+    };
+    return operands_stream(p) ? run(std::true_type{}) : run(std::false_type{});
 }
 
 static unsigned grid_for(int64_t work) { return (unsigned)std::min<int64_t>((work + kThreads - 1) / kThreads, 65536); }
@@ -810,7 +853,6 @@ __global__ __launch_bounds__(kThreads) void k_quantize_bf16(const float *X, int6
 // 2^e itself is beyond binary32) rounded to E4M3;
 // NaN stays NaN and an infinity saturates to +-448 like any |x 2^e| >= 464.
 // ws scale words: [0] = e_A, [1] = e_B, [2] = amax_A bits, [3] = amax_B bits.
-__global__ void k_amax_init(int *scale, int which) { scale[2 + which] = 0; }
 
 // 16-byte loads: rows of X are 16-byte aligned and k is a multiple of 4 (as for the quantizer).
 // |x| for finite x, else 0 (NaN and infinities take no part in the scale)
@@ -819,34 +861,66 @@ __device__ inline float fin_abs(float x) {
     return a <= 3.40282347e38f ? a : 0.0f;
 }
 
-__global__ __launch_bounds__(kThreads) void k_amax(const float *X, int64_t ldx, int64_t rows, int64_t k, int *scale,
-                                                   int which) {
+// One or both operands: blocks [0, nx) on x, the rest on y; each block's
+// maximum goes to its slot.  A wave takes runs of 2048 columns of a row, eight
+// loads in flight per lane and no division per load (one per element vector
+// held the pass at 3.5 TB/s).
+struct AmaxSide {
+    const float *X;
+    int64_t ldx, rows, k;
+    float *out;
+};
+template <bool NT>
+__global__ __launch_bounds__(kThreads) void k_amax(AmaxSide x, AmaxSide y, unsigned nx) {
     typedef float v4 __attribute__((ext_vector_type(4)));
+    constexpr int U = 8;
+    constexpr int64_t RUN = (int64_t)kWave * 4 * U;
     __shared__ float sh[kThreads / kWave];
+    const AmaxSide &o = blockIdx.x < nx ? x : y;
+    const unsigned blk = blockIdx.x < nx ? blockIdx.x : blockIdx.x - nx, nblk = blockIdx.x < nx ? nx : gridDim.x - nx;
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int64_t runs = (o.k + RUN - 1) / RUN, total = o.rows * runs;
     float mx = 0.0f;
-    const int64_t kv = k / 4, total = rows * kv;
-    for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < total; t += (int64_t)gridDim.x * kThreads) {
-        int64_t i = t / kv, l = (t - i * kv) * 4;
-        const v4 x = *(const v4 *)(X + i * ldx + l);
-        mx = fmaxf(mx, fmaxf(fmaxf(fin_abs(x[0]), fin_abs(x[1])), fmaxf(fin_abs(x[2]), fin_abs(x[3]))));
+    for (int64_t t = (int64_t)blk * (kThreads / kWave) + wave; t < total; t += (int64_t)nblk * (kThreads / kWave)) {
+        const int64_t i = t / runs, l0 = (t - i * runs) * RUN + lane * 4;
+        const float *row = o.X + i * o.ldx;
+        v4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t l = l0 + u * kWave * 4;
+            v[u] = l < o.k ? load_raw<NT, v4>(row + l) : v4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            mx = fmaxf(mx, fmaxf(fmaxf(fin_abs(v[u][0]), fin_abs(v[u][1])), fmaxf(fin_abs(v[u][2]), fin_abs(v[u][3]))));
     }
     for (int off = kWave / 2; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
-    if (threadIdx.x % kWave == 0) sh[threadIdx.x / kWave] = mx;
+    if (lane == 0) sh[wave] = mx;
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int q = 1; q < kThreads / kWave; ++q) mx = fmaxf(mx, sh[q]);
-        atomicMax((unsigned int *)&scale[2 + which], __float_as_uint(mx));
+        o.out[blk] = mx;
     }
 }
 
-__global__ void k_scale_exp(int *scale, int which) {
-    double amax = (double)__uint_as_float((unsigned int)scale[2 + which]);
-    int e = 0;
-    if (amax > 0.0 && amax <= 3.40282347e38) {        // finite by construction; both loops end within 160 steps
-        while (ldexp(amax, e + 1) <= 448.0) ++e;
-        while (ldexp(amax, e) > 448.0) --e;
-    }
-    scale[which] = e;
+// Block b: operand which + b, from its nx (b = 0) or ny block maxima.
+__global__ __launch_bounds__(kThreads) void k_scale_exp(const float *amax, int *scale, int which, unsigned nx,
+                                                        unsigned ny) {
+    __shared__ float sh[kThreads / kWave];
+    const int w = which + (int)blockIdx.x;
+    const unsigned n = blockIdx.x == 0 ? nx : ny;
+    float mx = 0.0f;
+    for (unsigned t = threadIdx.x; t < n; t += kThreads) mx = fmaxf(mx, amax[w * kAmaxBlocks + t]);
+    for (int off = kWave / 2; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
+    if (threadIdx.x % kWave == 0) sh[threadIdx.x / kWave] = mx;
+    __syncthreads();
+    if (threadIdx.x) return;
+    for (int q = 1; q < kThreads / kWave; ++q) mx = fmaxf(mx, sh[q]);
+    // mx = f 2^x with 0.5 <= f < 1 and 448 = 0.875 * 2^9
+    int e = 0, x = 0;
+    if (mx > 0.0f) e = (frexp((double)mx, &x) <= 0.875 ? 9 : 8) - x;
+    scale[2 + w] = (int)__float_as_uint(mx);
+    scale[w] = e;
 }
 
 __global__ __launch_bounds__(kThreads) void k_quantize_fp8(const float *X, int64_t ldx, int64_t rows, int64_t k,
@@ -857,12 +931,30 @@ __global__ __launch_bounds__(kThreads) void k_quantize_fp8(const float *X, int64
     for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < total; t += (int64_t)gridDim.x * kThreads) {
         int64_t i = t / per_row, c = (t - i * per_row) * 4;
         v4 x = *(const v4 *)(X + i * ldx + c);
-        uint32_t o = (uint32_t)f32_to_e4m3_rne(__builtin_ldexpf(x[0], e)) |
-                     ((uint32_t)f32_to_e4m3_rne(__builtin_ldexpf(x[1], e)) << 8) |
-                     ((uint32_t)f32_to_e4m3_rne(__builtin_ldexpf(x[2], e)) << 16) |
-                     ((uint32_t)f32_to_e4m3_rne(__builtin_ldexpf(x[3], e)) << 24);
+        const uint32_t o = f32x4_to_e4m3(__builtin_ldexpf(x[0], e), __builtin_ldexpf(x[1], e), __builtin_ldexpf(x[2], e),
+                                         __builtin_ldexpf(x[3], e));
         *(uint32_t *)(Q + i * ldq + c) = o;
     }
+}
+
+// Scale exponents of one operand (which) or of both (Y set, which = 0).
+static void scale_exponents(const abft_problem *p, int which, const float *X, int64_t ldx, const float *Y, int64_t ldy,
+                            char *ws, hipStream_t s) {
+    const WsLayout L = ws_layout(p);
+    float *amax = (float *)(ws + L.amax);
+    // the quantizing pass reads the operands again: kept in cache where both fit
+    const bool nt = streams((p->m + p->n) * p->k * 4);
+    auto side = [&](int w, const float *P, int64_t ld) {
+        return AmaxSide{P, ld, w == 0 ? p->m : p->n, p->k, amax + w * kAmaxBlocks};
+    };
+    auto blocks = [](const AmaxSide &a) {
+        return (unsigned)std::min<int64_t>((a.rows * ((a.k + 2047) / 2048) + 3) / 4, kAmaxBlocks);
+    };
+    const AmaxSide x = side(which, X, ldx), y = Y ? side(1, Y, ldy) : x;
+    const unsigned nx = blocks(x), ny = Y ? blocks(y) : 0;
+    if (nt) k_amax<true><<<nx + ny, kThreads, 0, s>>>(x, y, nx);
+    else k_amax<false><<<nx + ny, kThreads, 0, s>>>(x, y, nx);
+    k_scale_exp<<<Y ? 2 : 1, kThreads, 0, s>>>(amax, (int *)(ws + L.scale), which, nx, ny);
 }
 
 int launch_quantize(const abft_problem *p, int which, const float *X, int64_t ldx, void *dst, char *ws, hipStream_t s) {
@@ -876,10 +968,7 @@ int launch_quantize(const abft_problem *p, int which, const float *X, int64_t ld
     if (p->dtype == ABFT_FP8_E4M3) {
         WsLayout L = ws_layout(p);
         int *scale = (int *)(ws + L.scale);
-        k_amax_init<<<1, 1, 0, s>>>(scale, which);
-        k_amax<<<(unsigned)std::min<int64_t>((rows * p->k / 4 + kThreads - 1) / kThreads, 4096), kThreads, 0, s>>>(
-            X, ldx, rows, p->k, scale, which);
-        k_scale_exp<<<1, 1, 0, s>>>(scale, which);
+        scale_exponents(p, which, X, ldx, nullptr, 0, ws, s);
         k_quantize_fp8<<<grid_for(rows * p->k / 4), kThreads, 0, s>>>(X, ldx, rows, p->k, (uint8_t *)dst, ldq, scale,
                                                                       which);
         ABFT_LAUNCHED();
@@ -888,25 +977,30 @@ int launch_quantize(const abft_problem *p, int which, const float *X, int64_t ld
     return ABFT_E_UNSUPPORTED;
 }
 
-// Quantize both binary32 operands and encode them.  bfloat16: in the same
-// pass (the values abft_quantize would store are written and the encode uses
-// them as stored), so the result equals quantize + quantize + encode bit for
-// bit.  FP8: the separate passes, which measured faster than one pass that
-// rounds, decodes and sums 16 values per thread (absmax, quantize and encode
-// per operand).
+// Quantize both binary32 operands and encode them in the same pass (the values
+// abft_quantize would store are written and the encode uses them as stored),
+// so the result equals quantize + quantize + encode bit for bit.  FP8 reads
+// each operand once before that, for its scale.
 int launch_quantize_encode(const abft_problem *p, const float *A32, int64_t lda32, const float *B32, int64_t ldb32,
                            void *A_f, void *B_f, char *ws, hipStream_t s) {
     if (p->dtype == ABFT_BF16) {
         WsLayout L = ws_layout(p);
         uint16_t *A = (uint16_t *)A_f, *Bt = (uint16_t *)B_f;
-        return encode_typed<uint16_t, float>(p, SrcQuantBf16{A32, lda32, A, p->lda}, SrcQuantBf16{B32, ldb32, Bt, p->ldb},
-                                             A, Bt, (float *)(ws + L.acs), p->k, (float *)(ws + L.bcs), p->k, ws, s);
+        auto run = [&](auto nt) {
+            typedef SrcQuantBf16<decltype(nt)::value> Src;
+            return encode_typed<uint16_t, float>(p, Src{A32, lda32, A, p->lda}, Src{B32, ldb32, Bt, p->ldb}, A, Bt,
+                                                 (float *)(ws + L.acs), p->k, (float *)(ws + L.bcs), p->k, ws, s);
+        };
+        return operands_stream(p) ? run(std::true_type{}) : run(std::false_type{});
     }
     if (p->dtype == ABFT_FP8_E4M3) {
-        int st = launch_quantize(p, 0, A32, lda32, A_f, ws, s);
-        if (!st) st = launch_quantize(p, 1, B32, ldb32, B_f, ws, s);
-        if (!st) st = launch_encode(p, A_f, B_f, ws, s);
-        return st;
+        WsLayout L = ws_layout(p);
+        uint8_t *A = (uint8_t *)A_f, *Bt = (uint8_t *)B_f;
+        const int *scale = (const int *)(ws + L.scale);
+        scale_exponents(p, 0, A32, lda32, B32, ldb32, ws, s);
+        return encode_typed<uint8_t, float>(p, SrcQuantFp8{A32, lda32, A, p->lda, scale},
+                                            SrcQuantFp8{B32, ldb32, Bt, p->ldb, scale + 1}, A, Bt,
+                                            (float *)(ws + L.acs), p->k, (float *)(ws + L.bcs), p->k, ws, s);
     }
     return ABFT_E_UNSUPPORTED;
 }
