@@ -314,7 +314,7 @@ int launch_verify_fused(const abft_problem *p, const void *C_f, char *ws, int64_
 // the owner tag it stores in ws: a nonzero hash of the problem, the tile grid
 // and C_f.
 uint64_t fused_key(const abft_problem *p, const void *C_f, int64_t *tiles_m, int64_t *tiles_n);
-// Smallest tile edge of every product kernel: bounds the tile rows / columns of the fused partials.
+// Smallest tile edge of every product with fused partials: bounds their tile rows / columns.
 constexpr int64_t kMinTileEdge = 96;
 // Row tile of the one-pass b = 1 re-read verification (column sums per tile of this many rows); its row
 // sums are per tile of 64 16-byte vectors (128 binary64 or 256 binary32 columns).

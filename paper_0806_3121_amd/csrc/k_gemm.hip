@@ -23,9 +23,22 @@ constexpr int64_t kSliverMaxB = 8;
 
 struct TileChoice { int id; int bm, bn, per_cu; double eff; };
 
-// Estimated time ~ rounds of resident blocks x time per round (tile flops x
-// blocks per CU / per-tile efficiency); the smallest wins.  256 CUs.  Returns
-// the index of the pick in tab.
+// Estimated time ~ rounds x time per round (tile area / per-tile efficiency);
+// the smallest wins.  A round is one tile on each of the 256 CUs: tiles that
+// share a CU share its matrix cores, so only their number per CU counts.
+// Returns the index of the pick in tab.
+static int choose_rounds(const TileChoice *tab, int n, int64_t M, int64_t N) {
+    double best = 0;
+    int pick = 0;
+    for (int q = 0; q < n; ++q) {
+        const TileChoice &t = tab[q];
+        const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        const double cost = (double)((tiles + 255) / 256) * t.bm * t.bn / t.eff;
+        if (best == 0 || cost < best) { best = cost; pick = q; }
+    }
+    return pick;
+}
+// The same with rounds of per_cu resident tiles per CU.
 static int choose_tile(const TileChoice *tab, int n, int64_t M, int64_t N) {
     double best = 0;
     int pick = 0;
@@ -40,22 +53,35 @@ static int choose_tile(const TileChoice *tab, int n, int64_t M, int64_t N) {
     return pick;
 }
 
-// binary64 / binary32 direct-to-LDS candidates (K a multiple of the 128-byte slab); per-tile
-// efficiencies measured on MI355X at 8192^3 and 9216^2 x 8192 (binary64).  A 256 x 128 binary64
-// tile (0.85) is never cheaper than 128 x 128 at two blocks per CU and is not offered.
+// binary64 / binary32 direct-to-LDS candidates.  eff: share of the matrix
+// cores' rate with many rounds (at 2048 .. 9216 squared, k 2048 .. 16384), which orders
+// the tiles as measured, for instance (us, binary64 128x128 / 128x96 / 96x96 /
+// 64x64 / 32x32): 2048^3 241 / 354 / 271 / 248 / 294, 2001 x 1503 x 1234
+// 153 / 115 / 167 / 121 / 158, 5120 x 5120 x 4096 3260 / 3143 / 3171 / 3036 / 3626,
+// 1024^3 121 / 93 / 71 / 38 / 40, 512^3 63 / 48 / 37 / 19 / 8.7, 256^3
+// 34 / 26 / 21 / 11 / 7.7; binary32 256x128 / 128x128 / 64x64 / 32x32:
+// 2001 x 1503 x 1236 150 / 81 / 66 / 81, 2048^3 238 / 126 / 131 / 149.
+// A 256 x 128 binary64 tile measured the same as 128 x 128 and is not offered.
 static const TileChoice kF64DirectTiles[] = {
-    {1, 128, 128, 2, 0.87}, {2, 128, 96, 2, 0.89}, {3, 96, 96, 2, 0.88},
+    {1, 128, 128, 2, 0.94}, {2, 128, 96, 2, 0.935}, {3, 96, 96, 2, 0.94}, {4, 64, 64, 5, 0.90}, {5, 32, 32, 5, 0.75},
 };
 static const TileChoice kF32DirectTiles[] = {
+    {0, 256, 128, 1, 0.93}, {1, 128, 128, 2, 0.917}, {4, 64, 64, 2, 0.868}, {5, 32, 32, 5, 0.736},
+};
+// The fused partial sums in the workspace have room for tiles of this edge and more.
+constexpr int kF64FusedTiles = 3, kF32FusedTiles = 2;
+
+// Short and small products: the direct tiles at their rates with two blocks per CU, and the register-staged
+// kernel's for a ragged k.
+static const TileChoice kF64ShortTiles[] = {
+    {1, 128, 128, 2, 0.87}, {2, 128, 96, 2, 0.89}, {3, 96, 96, 2, 0.88},
+};
+static const TileChoice kF32ShortTiles[] = {
     {0, 256, 128, 1, 0.85}, {1, 128, 128, 2, 0.84},
 };
-
-// binary64 candidates of the register-staged kernel (any even K); efficiencies measured on MI355X at
-// 8192^3 and 9216^2 x 8192.
 static const TileChoice kF64Tiles[] = {
     {0, 256, 128, 1, 0.818}, {1, 128, 128, 2, 0.787}, {2, 128, 96, 2, 0.80}, {3, 96, 96, 2, 0.76},
 };
-// binary32 candidates (same shapes; the f32 matrix core is twice as fast per instruction).
 static const TileChoice kF32Tiles[] = {
     {0, 256, 128, 1, 0.80}, {1, 128, 128, 2, 0.78},
 };
@@ -65,18 +91,36 @@ struct MainPick {
     bool direct;            // direct-to-LDS kernel (else register-staged / padded-LDS)
     const TileChoice *t;
 };
-static MainPick pick_main(const double *, int64_t M, int64_t N, int64_t K) {
-    if (K % 16 == 0) return {true, &kF64DirectTiles[choose_tile(kF64DirectTiles, 3, M, N)]};
+// Whether an M x N x K product (K in slabs of BK) is picked from the direct
+// tiles by rounds.  Below four slabs a launch is mostly its start and its
+// stores and the pick matters little (binary64 776 x 5384 x 32: 13 us with any
+// tile; 1032 x 5384 x 48: 17 to 23), and so it does for the small products of
+// a ragged k or a fused epilogue excluded here (320 x 320 x 250: 21 us against
+// 8): these stay with the short table and the register-staged kernel, whose
+// tiles are checked at just such sizes.
+static bool by_rounds(int64_t M, int64_t N, int64_t K, int64_t BK, bool fused) {
+    const int64_t least = fused ? int64_t(1) << 18 : (K % BK ? int64_t(1) << 17 : 0);
+    return K >= 4 * BK && M * N > least;
+}
+static MainPick pick_main(const double *, int64_t M, int64_t N, int64_t K, bool fused) {
+    if (by_rounds(M, N, K, 16, fused)) {
+        // a ragged k needs a few more registers than 128 x 128 leaves free
+        const int skip = K % 16 ? 1 : 0, n = (fused ? kF64FusedTiles : 5) - skip;
+        return {true, &kF64DirectTiles[skip + choose_rounds(kF64DirectTiles + skip, n, M, N)]};
+    }
+    if (K % 16 == 0) return {true, &kF64ShortTiles[choose_tile(kF64ShortTiles, 3, M, N)]};
     return {false, &kF64Tiles[choose_tile(kF64Tiles, 4, M, N)]};
 }
-static MainPick pick_main(const float *, int64_t M, int64_t N, int64_t K) {
-    if (K % 32 == 0) return {true, &kF32DirectTiles[choose_tile(kF32DirectTiles, 2, M, N)]};
+static MainPick pick_main(const float *, int64_t M, int64_t N, int64_t K, bool fused) {
+    if (by_rounds(M, N, K, 32, fused))
+        return {true, &kF32DirectTiles[choose_rounds(kF32DirectTiles, fused ? kF32FusedTiles : 4, M, N)]};
+    if (K % 32 == 0) return {true, &kF32ShortTiles[choose_tile(kF32ShortTiles, 2, M, N)]};
     return {false, &kF32Tiles[choose_tile(kF32Tiles, 2, M, N)]};
 }
 
 static int gemm_main(const double *A, int64_t lda, const double *Bt, int64_t ldb, double *C, int64_t ldc, int64_t M,
                      int64_t N, int64_t K, hipStream_t s, bool acc = false, EpiArgs *e = nullptr) {
-    const MainPick pk = pick_main(A, M, N, K);
+    const MainPick pk = pick_main(A, M, N, K, e && e->pc);
     if (pk.direct) {
         switch (pk.t->id) {
         case 1:
@@ -85,6 +129,10 @@ static int gemm_main(const double *A, int64_t lda, const double *Bt, int64_t ldb
         case 2:
             return launch_gemm_mfma2<Mfma2Tile<double, 2, 128, 96, 2, 2, 2>>(A, lda, Bt, ldb, C, ldc, M, N, K, s, acc,
                                                                             e);
+        case 4:
+            return launch_gemm_mfma2<Mfma2Tile<double, 2, 64, 64, 2, 2, 4>>(A, lda, Bt, ldb, C, ldc, M, N, K, s, acc, e);
+        case 5:
+            return launch_gemm_mfma2<Mfma2Tile<double, 4, 32, 32, 2, 2, 4>>(A, lda, Bt, ldb, C, ldc, M, N, K, s, acc, e);
         default:
             return launch_gemm_mfma2<Mfma2Tile<double, 2, 96, 96, 2, 2, 2>>(A, lda, Bt, ldb, C, ldc, M, N, K, s, acc,
                                                                            e);
@@ -103,10 +151,14 @@ static int gemm_main(const double *A, int64_t lda, const double *Bt, int64_t ldb
 
 static int gemm_main(const float *A, int64_t lda, const float *Bt, int64_t ldb, float *C, int64_t ldc, int64_t M,
                      int64_t N, int64_t K, hipStream_t s, bool acc = false, EpiArgs *e = nullptr) {
-    const MainPick pk = pick_main(A, M, N, K);
+    const MainPick pk = pick_main(A, M, N, K, e && e->pc);
     if (pk.direct) {
         switch (pk.t->id) {
         case 0: return launch_gemm_mfma2<Mfma2Tile<float, 2>>(A, lda, Bt, ldb, C, ldc, M, N, K, s, acc, e);
+        case 4:
+            return launch_gemm_mfma2<Mfma2Tile<float, 4, 64, 64, 2, 2, 2>>(A, lda, Bt, ldb, C, ldc, M, N, K, s, acc, e);
+        case 5:
+            return launch_gemm_mfma2<Mfma2Tile<float, 4, 32, 32, 2, 2, 4>>(A, lda, Bt, ldb, C, ldc, M, N, K, s, acc, e);
         default:
             return launch_gemm_mfma2<Mfma2Tile<float, 2, 128, 128, 2, 2, 2>>(A, lda, Bt, ldb, C, ldc, M, N, K, s, acc,
                                                                             e);
@@ -263,8 +315,8 @@ int describe_gemm(const abft_problem *p, uint32_t flags, char *buf, size_t len) 
         thin_c = !plain && g.S * g.bc <= kSliverMaxB;
         Mm = (plain || thin_r) ? g.m : g.M;
         Nm = (plain || thin_c) ? g.n : g.N;
-        pk = p->dtype == ABFT_F64 ? pick_main((const double *)nullptr, Mm, Nm, g.k)
-                                  : pick_main((const float *)nullptr, Mm, Nm, g.k);
+        pk = p->dtype == ABFT_F64 ? pick_main((const double *)nullptr, Mm, Nm, g.k, flags & ABFT_FUSED)
+                                  : pick_main((const float *)nullptr, Mm, Nm, g.k, flags & ABFT_FUSED);
         kname = pk.direct ? "k_gemm_mfma2" : "k_gemm_mfma";
     }
     // the carried blocks' kernels: rows over the N columns (lowp: n), columns over the data rows
@@ -291,8 +343,8 @@ uint64_t fused_key(const abft_problem *p, const void *C_f, int64_t *tiles_m, int
     const bool lowp = p->dtype == ABFT_BF16 || p->dtype == ABFT_FP8_E4M3;
     // b = 1: the carried row and column are slivers, the main product covers m x n
     const MainPick pk = lowp ? pick_main_lowp(p->dtype == ABFT_BF16 ? 2 : 1, g.m, g.n, g.k)
-                             : (p->dtype == ABFT_F64 ? pick_main((const double *)nullptr, g.m, g.n, g.k)
-                                                     : pick_main((const float *)nullptr, g.m, g.n, g.k));
+                             : (p->dtype == ABFT_F64 ? pick_main((const double *)nullptr, g.m, g.n, g.k, true)
+                                                     : pick_main((const float *)nullptr, g.m, g.n, g.k, true));
     *tiles_m = (g.m + pk.t->bm - 1) / pk.t->bm;
     *tiles_n = (g.n + pk.t->bn - 1) / pk.t->bn;
     uint64_t h = 0x6A09E667F3BCC908ull;
