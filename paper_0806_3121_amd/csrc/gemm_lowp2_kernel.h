@@ -163,12 +163,14 @@ __global__ __launch_bounds__(128 * WM, 1) void k_gemm_lowp2(const typename Ops::
             read(x, 1, fa1, fb1);
             mma(fa0, fb0);
             spread_reads();
+            __builtin_amdgcn_sched_barrier(0);
             __builtin_amdgcn_s_waitcnt(0x0070);    // vmcnt(0) lgkmcnt(0)
             bare_barrier();
             issue(x, (kt + 2) * BK);
             read(x ^ 1, 0, fa0, fb0);
             mma(fa1, fb1);
             spread_loads_reads();
+            __builtin_amdgcn_sched_barrier(0);
         }
         if (kt + 2 == nk) {                        // two slabs left: no more loads
             const int x = (int)(kt & 1);
@@ -283,12 +285,14 @@ __global__ __launch_bounds__(128 * WM, 1) void k_gemm_lowp2(const typename Ops::
             read(x, 1, fa1, fb1);
             mma(fa0, fb0);
             spread_reads();
+            __builtin_amdgcn_sched_barrier(0);
             __builtin_amdgcn_s_waitcnt(0x0070);    // vmcnt(0) lgkmcnt(0)
             bare_barrier();
             issue(x, (kt + 2) * BK);
             read(x ^ 1, 0, fa0, fb0);
             mma(fa1, fb1);
             spread_loads_reads();
+            __builtin_amdgcn_sched_barrier(0);
         }
         for (; kt < nk; ++kt) {                    // the last one or two slabs
             const int x = (int)(kt & 1);
