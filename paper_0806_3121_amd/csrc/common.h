@@ -155,6 +155,21 @@ template <> struct vec16<uint8_t> {                  // FP8 E4M3
 };
 
 
+// Streaming (non-temporal) access: a pass over data far larger than the caches
+// is faster with it -- the FP8 scale's read of two 8192 x 8192 binary32
+// operands 107 -> 81 us (6.6 TB/s), the binary64 encode of two 8192 x 8192
+// operands 263 -> 243, the bfloat16 values stored by the quantizing pass over a
+// 16384 x 16384 operand 341 -> 319 -- while data that fits the 256 MB
+// memory-side cache is left there for the pass or the product that reads it next.
+// Also the carried-row and matrix-vector products' operand rows (k_sliver), see there.
+// The quantizing passes' own loads gain nothing from it (FP8: 62 -> 67 us, the
+// scale's read leaves part of the operand in that cache).
+inline bool streams(int64_t bytes) { return bytes > (int64_t(256) << 20); }
+template <bool NT, typename R> __device__ inline R load_raw(const void *p) {
+    if constexpr (NT) return __builtin_nontemporal_load((const R *)p);
+    else return *(const R *)p;
+}
+
 inline size_t dtype_size(int dt) {
     switch (dt) {
     case ABFT_F64: return 8;

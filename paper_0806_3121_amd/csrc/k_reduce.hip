@@ -102,21 +102,8 @@ __device__ inline double row_term(int mode, double x, double w) {
     return mode == ROW_W ? x2 * w : (mode == ROW_L4SQ ? x2 * x2 : x2);
 }
 
-// Streaming (non-temporal) access: a pass over data far larger than the caches
-// is faster with it -- the FP8 scale's read of two 8192 x 8192 binary32
-// operands 107 -> 81 us (6.6 TB/s), the binary64 encode of two 8192 x 8192
-// operands 263 -> 243, the bfloat16 values stored by the quantizing pass over a
-// 16384 x 16384 operand 341 -> 319 -- while data that fits the 256 MB
-// memory-side cache is left there for the pass or the product that reads it next.
-// The quantizing passes' own loads gain nothing from it (FP8: 62 -> 67 us, the
-// scale's read leaves part of the operand in that cache).
-static bool streams(int64_t bytes) { return bytes > (int64_t(256) << 20); }
 static bool operands_stream(const abft_problem *p) {
     return streams((p->m + p->n) * p->k * (int64_t)dtype_size(p->dtype));
-}
-template <bool NT, typename R> __device__ inline R load_raw(const void *p) {
-    if constexpr (NT) return __builtin_nontemporal_load((const R *)p);
-    else return *(const R *)p;
 }
 
 // Where the encode pass takes an operand's values from: the stored operand,

@@ -40,7 +40,7 @@ WGeom wgeom(const abft_wproblem *p) {
 size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct WLayout {
-    size_t wr, wc, na, nb, s1, s2, part, report, total;
+    size_t wr, wc, na, nb, s1, s2, part, report, rowa, rowb, total;
 };
 
 // Partitions of a (G blocks x rel relations) sum: independent sums enough to
@@ -60,7 +60,7 @@ WLayout wlayout(const WGeom &g) {
     L.nb = take(sizeof(double) * g.N);
     L.s1 = take(sizeof(double) * g.fr * g.br);
     L.s2 = take(sizeof(double) * g.fc * g.bc);
-    int64_t kv = g.k / g.V;
+    const int64_t kv = g.k / g.V;
     size_t pa = 0;
     int64_t P = parts(g.Gr, g.br * kv);
     if (P > 1) pa = std::max(pa, (size_t)(P * g.fr * g.br * g.k));
@@ -70,6 +70,10 @@ WLayout wlayout(const WGeom &g) {
     if (P > 1) pa = std::max(pa, (size_t)(P * g.fr * g.br * g.N));
     L.part = take(sizeof(double) * std::max<size_t>(pa, 1));
     L.report = take(sizeof(abft_wreport));
+    // row-norm partials of the fused encode: a slot per strip of 64 vectors
+    const int64_t strips = (kv + kW - 1) / kW;
+    L.rowa = take(parts(g.Gr, g.br * kv) == 1 ? sizeof(double) * g.M * strips : 8);
+    L.rowb = take(parts(g.Gc, g.bc * kv) == 1 ? sizeof(double) * g.N * strips : 8);
     L.total = off;
     return L;
 }
@@ -140,16 +144,125 @@ __device__ inline double group(abft_wreport *rep, bool col, int64_t a, int64_t b
 // stored result is rounded once to T.  V = elements per 16-byte load.
 template <typename T> __device__ inline double ld(const T *p) { return (double)*p; }
 
-// Checksum rows out[r*b + i, l] = sum_g W[r][g] X[g*b + i, l] for the blocks
-// [g0, g1); X has rows of k elements (16-byte aligned, k a multiple of V).
-// P == 1: outT is the checksum rows (row r*b + i, leading dimension ldo),
-// rounded to T; P > 1: part is the binary64 partial buffer, partition p at
-// p*rstride.
+// Encode of one operand in one read, for enough relations to fill the chip
+// with one lane each: a wave owns a strip of 64 vectors of one residue i and
+// walks its G blocks (four rows requested together), keeping the F checksum
+// rows' sums in block order, and writes each row's partial sum of squares
+// rp[strip * rows + row] -- data rows, and the checksum rows as stored -- from
+// the same read.  HBM-bound; X is 16-byte aligned in every row and k a multiple
+// of V.  NT: the operand is larger than the caches.  The separate passes read A
+// twice: 447 + 429 us for 16384 x 16384 binary64, f = 2; here 400 (5.7 TB/s; 413
+// without the next rows requested ahead, 431 with the partials row by row).
+template <int F, typename T, bool NT>
+__global__ __launch_bounds__(kT) void k_wenc_rows(const T *__restrict__ X, int64_t ld_, int64_t b, int64_t G, int64_t k,
+                                                  const double *__restrict__ W, T *__restrict__ out, int64_t strips,
+                                                  double *__restrict__ rp) {
+    constexpr int V = vec16<T>::N, U = 4;
+    const int64_t strip = blockIdx.x % strips;
+    const int64_t i = blockIdx.x / strips * (kT / kW) + __builtin_amdgcn_readfirstlane(threadIdx.x / kW);
+    if (i >= b) return;
+    const int lane = threadIdx.x % kW;
+    const int64_t kv = k / V, cv = strip * kW + lane, l = min(cv, kv - 1) * V;
+    const bool ok = cv < kv;
+    const int64_t rows = (G + F) * b;
+    double s[F][V] = {};
+    auto add = [&](const v4u32 &raw, int64_t g) {
+        double q2 = 0.0;
+        if (ok) {
+            double v[V];
+            vec16<T>::widen(raw, v);
+#pragma unroll
+            for (int r = 0; r < F; ++r) {
+                const double w = W[r * G + g];
+#pragma unroll
+                for (int e = 0; e < V; ++e) s[r][e] += w * v[e];
+            }
+#pragma unroll
+            for (int e = 0; e < V; ++e) q2 += v[e] * v[e];
+        }
+        return q2;
+    };
+    auto put = [&](double q2, int64_t row) {
+        q2 = wsum(q2);
+        if (lane == 0) rp[strip * rows + row] = q2;
+    };
+    // the next four rows are requested before the four in hand are summed
+    auto request = [&](v4u32 (&raw)[U], int64_t g) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (ok) raw[u] = load_raw<NT, v4u32>(X + ((g + u) * b + i) * ld_ + l);
+    };
+    int64_t g = 0;
+    v4u32 next[U];
+    if (U <= G) request(next, 0);
+    for (; g + U <= G; g += U) {
+        v4u32 raw[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) raw[u] = next[u];
+        if (g + 2 * U <= G) request(next, g + U);
+        double q[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) q[u] = add(raw[u], g + u);
+        // four rows' sums by a reduce-scatter: 2 + 1 exchanges, then within 16 lanes
+        const bool hi = lane & 32, lo = lane & 16;
+        double k0 = hi ? q[2] : q[0], k1 = hi ? q[3] : q[1];
+        k0 += __shfl_xor(hi ? q[0] : q[2], 32);
+        k1 += __shfl_xor(hi ? q[1] : q[3], 32);
+        double x = lo ? k1 : k0;
+        x += __shfl_xor(lo ? k0 : k1, 16);
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) x += __shfl_xor(x, o);
+        if (lane % 16 == 0) rp[strip * rows + (g + lane / 16) * b + i] = x;
+    }
+    for (; g < G; ++g) {
+        v4u32 raw;
+        if (ok) raw = load_raw<NT, v4u32>(X + (g * b + i) * ld_ + l);
+        put(add(raw, g), g * b + i);
+    }
+#pragma unroll
+    for (int r = 0; r < F; ++r) {
+        double q2 = 0.0;
+        if (ok) {
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                const T y = (T)s[r][e];
+                out[(r * b + i) * ld_ + l + e] = y;
+                q2 += (double)y * (double)y;
+            }
+        }
+        put(q2, (G + r) * b + i);
+    }
+}
+
+// Row norms of both operands from those partials: rows [0, na) are A_f's, the
+// rest B_f's; an operand encoded in separate passes has none.  A block takes 64
+// rows, its four waves every fourth strip.
+__global__ __launch_bounds__(kT) void k_wrow_norms(const double *__restrict__ pa, int64_t na, const double *__restrict__ pb,
+                                                   int64_t nb, int64_t strips, double *__restrict__ outa,
+                                                   double *__restrict__ outb) {
+    __shared__ double sh[kT / kW][kW];
+    const int lane = threadIdx.x % kW, w = threadIdx.x / kW;
+    const int64_t x = (int64_t)blockIdx.x * kW + lane;
+    double s = 0.0;
+    if (x < na + nb) {
+        const double *p = x < na ? pa + x : pb + (x - na);
+        const int64_t rows = x < na ? na : nb;
+        for (int64_t c = w; c < strips; c += kT / kW) s += p[c * rows];
+    }
+    sh[w][lane] = s;
+    __syncthreads();
+    if (w || x >= na + nb) return;
+    s = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
+    (x < na ? outa[x] : outb[x - na]) = sqrt(s);
+}
+
+// Partial checksum rows part[p][r*b + i, l] = sum_g W[r][g] X[g*b + i, l] over
+// partition p's blocks g (binary64, rstride elements per partition); X has rows
+// of k elements (16-byte aligned, k a multiple of V).
 template <int F, typename T>
 __global__ __launch_bounds__(kT) void k_wenc(const T *__restrict__ X, int64_t ld_, int64_t b, int64_t G, int64_t k,
                                              const double *__restrict__ W, int64_t P, int64_t chunk,
-                                             T *__restrict__ outT, double *__restrict__ part, int64_t ldo,
-                                             int64_t rstride) {
+                                             double *__restrict__ part, int64_t rstride) {
     constexpr int V = vec16<T>::N;
     const int64_t kv = k / V, total = P * b * kv;
     for (int64_t t = (int64_t)blockIdx.x * kT + threadIdx.x; t < total; t += (int64_t)gridDim.x * kT) {
@@ -171,18 +284,11 @@ __global__ __launch_bounds__(kT) void k_wenc(const T *__restrict__ X, int64_t ld
                 for (int e = 0; e < V; ++e) s[r][e] += w * v[e];
             }
         }
-        if (P == 1) {
+        double *o = part + p * rstride;
 #pragma unroll
-            for (int r = 0; r < F; ++r)
+        for (int r = 0; r < F; ++r)
 #pragma unroll
-                for (int e = 0; e < V; ++e) outT[(r * b + i) * ldo + l + e] = (T)s[r][e];
-        } else {
-            double *o = part + p * rstride;
-#pragma unroll
-            for (int r = 0; r < F; ++r)
-#pragma unroll
-                for (int e = 0; e < V; ++e) o[(r * b + i) * k + l + e] = s[r][e];
-        }
+            for (int e = 0; e < V; ++e) o[(r * b + i) * k + l + e] = s[r][e];
     }
 }
 
@@ -220,15 +326,20 @@ __global__ __launch_bounds__(kT) void k_wnorm(const T *__restrict__ X, int64_t l
     }
 }
 
-// S[r*b + i] = sum_g |W[r][g]| nrm[g*b + i]
-__global__ __launch_bounds__(kT) void k_wsumnorm(const double *__restrict__ W, int f, int64_t G, int64_t b,
-                                                 const double *__restrict__ nrm, double *__restrict__ S) {
-    const int64_t total = f * b;
+// S[r*b + i] = sum_g |W[r][g]| nrm[g*b + i], of both operands in one launch
+struct SumNorm {
+    const double *W, *nrm;
+    double *S;
+    int64_t f, G, b;
+};
+__global__ __launch_bounds__(kT) void k_wsumnorm(SumNorm x, SumNorm y) {
+    const int64_t nx = x.f * x.b, total = nx + y.f * y.b;
     for (int64_t t = (int64_t)blockIdx.x * kT + threadIdx.x; t < total; t += (int64_t)gridDim.x * kT) {
-        const int64_t r = t / b, i = t - r * b;
+        const SumNorm &o = t < nx ? x : y;
+        const int64_t q = t < nx ? t : t - nx, r = q / o.b, i = q - r * o.b;
         double s = 0.0;
-        for (int64_t g = 0; g < G; ++g) s += fabs(W[r * G + g]) * nrm[g * b + i];
-        S[t] = s;
+        for (int64_t g = 0; g < o.G; ++g) s += fabs(o.W[r * o.G + g]) * o.nrm[g * o.b + i];
+        o.S[q] = s;
     }
 }
 
@@ -627,23 +738,52 @@ int launch_recover_any(int dtype, void *C, const RArgs &a, hipStream_t s) {
 }
 
 // Weighted checksum rows of one operand (rows of A_f, or rows of B_f^T):
-// out = X + G*b*ld, one pass (P == 1) or binary64 partial sums then their
-// ordered sum; stored rounded once to T.
+// out = X + G*b*ld, stored rounded once to T, and the norms of its rows.  With
+// one partition in one read (row-norm partials in rp, finished by the caller:
+// *fused); otherwise binary64 partial sums, their ordered sum and a pass over
+// the rows.
 template <typename T>
 int encode_side(const T *X, int64_t ld_, int64_t G, int64_t b, int64_t k, int f, const double *W, double *part,
-                hipStream_t s) {
+                double *rp, double *nrm, bool nt, bool *fused, hipStream_t s) {
     T *out = const_cast<T *>(X) + G * b * ld_;
     const int64_t kv = k / vec16<T>::N;
     int64_t P = parts(G, b * kv);
+    *fused = P == 1;
     if (P == 1) {
-        WSWITCH(f, (k_wenc<F, T><<<grid(b * kv), kT, 0, s>>>(X, ld_, b, G, k, W, 1, G, out, nullptr, ld_, 0)));
+        const int64_t strips = (kv + kW - 1) / kW, blocks = strips * ((b + kT / kW - 1) / (kT / kW));
+        if (blocks > INT32_MAX) return ABFT_E_ARG;
+        if (nt) {
+            WSWITCH(f, (k_wenc_rows<F, T, true><<<(unsigned)blocks, kT, 0, s>>>(X, ld_, b, G, k, W, out, strips, rp)));
+        } else {
+            WSWITCH(f, (k_wenc_rows<F, T, false><<<(unsigned)blocks, kT, 0, s>>>(X, ld_, b, G, k, W, out, strips, rp)));
+        }
     } else {
         const int64_t chunk = (G + P - 1) / P;
         P = (G + chunk - 1) / chunk;
-        WSWITCH(f, (k_wenc<F, T><<<grid(P * b * kv), kT, 0, s>>>(X, ld_, b, G, k, W, P, chunk, nullptr, part, ld_,
-                                                                  f * b * k)));
+        WSWITCH(f, (k_wenc<F, T><<<grid(P * b * kv), kT, 0, s>>>(X, ld_, b, G, k, W, P, chunk, part, f * b * k)));
         k_wpart_sum<T><<<grid(f * b * k), kT, 0, s>>>(part, P, f * b, k, out, ld_);
+        const int64_t rows = (G + f) * b;
+        k_wnorm<T><<<grid(rows * kW), kT, 0, s>>>(X, ld_, rows, k, nrm);
     }
+    ABFT_LAUNCHED();
+    return ABFT_OK;
+}
+
+// Both operands, then the norms and their weighted sums.
+template <typename T>
+int encode_both(const WGeom &g, const WLayout &L, T *A, T *B, char *w, hipStream_t s) {
+    const double *wr = (const double *)(w + L.wr), *wc = (const double *)(w + L.wc);
+    double *part = (double *)(w + L.part), *na = (double *)(w + L.na), *nb = (double *)(w + L.nb);
+    double *ra = (double *)(w + L.rowa), *rb = (double *)(w + L.rowb);
+    const bool nt = streams((g.M + g.N) * g.k * (int64_t)sizeof(T));
+    bool fa = false, fb = false;
+    int st = encode_side(A, g.lda, g.Gr, g.br, g.k, g.fr, wr, part, ra, na, nt, &fa, s);
+    if (!st) st = encode_side(B, g.ldb, g.Gc, g.bc, g.k, g.fc, wc, part, rb, nb, nt, &fb, s);
+    if (st) return st;
+    const int64_t ma = fa ? g.M : 0, mb = fb ? g.N : 0, strips = (g.k / g.V + kW - 1) / kW;
+    if (ma + mb) k_wrow_norms<<<(unsigned)((ma + mb + kW - 1) / kW), kT, 0, s>>>(ra, ma, rb, mb, strips, na, nb);
+    k_wsumnorm<<<grid(g.fr * g.br + g.fc * g.bc), kT, 0, s>>>(
+        SumNorm{wr, na, (double *)(w + L.s1), g.fr, g.Gr, g.br}, SumNorm{wc, nb, (double *)(w + L.s2), g.fc, g.Gc, g.bc});
     ABFT_LAUNCHED();
     return ABFT_OK;
 }
@@ -728,25 +868,8 @@ int abft_wencode(const abft_wproblem *p, void *A_f, void *B_f, void *ws, size_t 
     const WLayout L = wlayout(g);
     hipStream_t s = (hipStream_t)stream;
     char *w = (char *)ws;
-    double *part = (double *)(w + L.part);
-    const double *wr = (const double *)(w + L.wr), *wc = (const double *)(w + L.wc);
-    if (g.dtype == ABFT_F64) {
-        if ((st = encode_side((const double *)A_f, g.lda, g.Gr, g.br, g.k, g.fr, wr, part, s))) return st;
-        if ((st = encode_side((const double *)B_f, g.ldb, g.Gc, g.bc, g.k, g.fc, wc, part, s))) return st;
-        k_wnorm<double><<<grid(g.M * kW), kT, 0, s>>>((const double *)A_f, g.lda, g.M, g.k, (double *)(w + L.na));
-        k_wnorm<double><<<grid(g.N * kW), kT, 0, s>>>((const double *)B_f, g.ldb, g.N, g.k, (double *)(w + L.nb));
-    } else {
-        if ((st = encode_side((const float *)A_f, g.lda, g.Gr, g.br, g.k, g.fr, wr, part, s))) return st;
-        if ((st = encode_side((const float *)B_f, g.ldb, g.Gc, g.bc, g.k, g.fc, wc, part, s))) return st;
-        k_wnorm<float><<<grid(g.M * kW), kT, 0, s>>>((const float *)A_f, g.lda, g.M, g.k, (double *)(w + L.na));
-        k_wnorm<float><<<grid(g.N * kW), kT, 0, s>>>((const float *)B_f, g.ldb, g.N, g.k, (double *)(w + L.nb));
-    }
-    k_wsumnorm<<<grid(g.fr * g.br), kT, 0, s>>>((const double *)(w + L.wr), g.fr, g.Gr, g.br,
-                                                (const double *)(w + L.na), (double *)(w + L.s1));
-    k_wsumnorm<<<grid(g.fc * g.bc), kT, 0, s>>>((const double *)(w + L.wc), g.fc, g.Gc, g.bc,
-                                                (const double *)(w + L.nb), (double *)(w + L.s2));
-    ABFT_LAUNCHED();
-    return ABFT_OK;
+    if (g.dtype == ABFT_F64) return encode_both(g, L, (double *)A_f, (double *)B_f, w, s);
+    return encode_both(g, L, (float *)A_f, (float *)B_f, w, s);
 }
 
 int abft_wgemm(const abft_wproblem *p, const void *A_f, const void *B_f, void *C_f, void *stream) {
