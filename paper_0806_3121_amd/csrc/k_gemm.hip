@@ -170,11 +170,28 @@ static int gemm_main(const float *A, int64_t lda, const float *Bt, int64_t ldb, 
     }
 }
 
+// Where the owner tag of the fused partial sums is still to be stored; its
+// value depends on the tile grid the main launch has filled in.  The carried
+// blocks' launch stores it and clears dst.
+struct TagStore {
+    uint64_t *dst;
+    const abft_problem *p;
+    const void *C_f;
+    bool fused;
+    const EpiArgs *e;
+    uint64_t key() const {
+        if (!fused) return 0;
+        int64_t tm = 0, tn = 0;
+        const uint64_t k = fused_key(p, C_f, &tm, &tn);
+        return tm == e->tiles_m && tn == e->tiles_n ? k : 0;   // 0: a grid the fused verification would not read
+    }
+};
+
 // C_f = (acc ? C_f : 0) + A_f[:, k0:k0+K) B_f[k0:k0+K, :)  (the whole product: k0 = 0, K = k).
 template <typename E>
 static int protected_product(const abft_problem *p, const Geom &g, const E *A, const E *Bt, E *C, bool plain,
                              hipStream_t s, int64_t k0 = 0, int64_t K = -1, bool acc = false,
-                             EpiArgs *e = nullptr) {
+                             EpiArgs *e = nullptr, TagStore *tag = nullptr) {
     if (K < 0) K = g.k;
     const bool thin_r = !plain && g.S * g.br <= kSliverMaxB;
     const bool thin_c = !plain && g.S * g.bc <= kSliverMaxB;
@@ -184,13 +201,15 @@ static int protected_product(const abft_problem *p, const Geom &g, const E *A, c
     int st = gemm_main(Ak, p->lda, Bk, p->ldb, C, p->ldc, Mm, Nm, K, s, acc, e);
     if (st) return st;
     ABFT_LAUNCHED();
-    // carried row block over all N columns (corner included), then the carried
-    // column block over the rows the main product covered
-    if (thin_r && (st = launch_sliver_rows<E, E, E>(g, Ak + g.m * p->lda, p->lda, Bk, p->ldb, C, p->ldc, K, acc, s)))
-        return st;
-    if (thin_c &&
-        (st = launch_sliver_cols<E, E, E>(g, Mm, Ak, p->lda, Bk + g.n * p->ldb, p->ldb, C, p->ldc, K, acc, s)))
-        return st;
+    // the carried row block over all N columns (corner included) and the carried
+    // column block over the rows the main product covered, in one launch
+    SliverExtra x = sliver_extra(nullptr, acc);
+    if (tag && (thin_r || thin_c)) { x.tag = tag->dst; x.key = tag->key(); tag->dst = nullptr; }
+    const auto cols = sliver_carried_cols<E>(g, Mm, Ak, p->lda, Bk + g.n * p->ldb, p->ldb, C, p->ldc, K);
+    if (thin_r)
+        return slivers(sliver_carried_rows<E>(g, Ak + g.m * p->lda, p->lda, Bk, p->ldb, C, p->ldc, K),
+                       thin_c ? &cols : nullptr, x, s);
+    if (thin_c) return slivers(cols, (decltype(&cols))nullptr, x, s);
     return ABFT_OK;
 }
 
@@ -229,28 +248,28 @@ static int gemm_main_lowp(const typename Ops::E *A, int64_t lda, const typename 
 template <class Ops, class Ops2>
 static int protected_product_lowp(const abft_problem *p, const Geom &g, const typename Ops::E *A,
                                   const typename Ops::E *Bt, float *C, const float *Acs, const float *Bcs,
-                                  const int *scale_exp, bool plain, hipStream_t s, EpiArgs *e = nullptr) {
+                                  const int *scale_exp, bool plain, hipStream_t s, EpiArgs *e = nullptr,
+                                  TagStore *tag = nullptr) {
     typedef typename Ops::E E;
     int st = gemm_main_lowp<Ops, Ops2>(A, p->lda, Bt, p->ldb, C, p->ldc, g.m, g.n, g.k, scale_exp, s, e);
     if (st) return st;
     ABFT_LAUNCHED();
     if (plain) return ABFT_OK;
     float *Crow = C + g.m * p->ldc;
-    // C_f[m + r, j], j < n
-    if ((st = sliver<E, float, float>(Bt, p->ldb, g.n, Acs, g.k, g.br, g.k, Crow, 1, p->ldc, scale_exp, s))) return st;
+    SliverExtra x = sliver_extra(scale_exp, false);
     // corner C_f[m + r, n + c]
-    if ((st = sliver<float, float, float>(Bcs, g.k, g.bc, Acs, g.k, g.br, g.k, Crow + g.n, 1, p->ldc, scale_exp, s)))
-        return st;
-    // C_f[i, n + c], i < m
-    return sliver<E, float, float>(A, p->lda, g.m, Bcs, g.k, g.bc, g.k, C + g.n, p->ldc, 1, scale_exp, s);
+    x.Yr = Acs; x.Yc = Bcs; x.K = g.k; x.nc = g.bc; x.out = Crow + g.n; x.ldo = p->ldc;
+    x.blocks = (unsigned)(g.br * g.bc);
+    if (tag) { x.tag = tag->dst; x.key = tag->key(); tag->dst = nullptr; }
+    // C_f[m + r, j], j < n, and C_f[i, n + c], i < m
+    const auto cols = sliver_job<E, float, float>(A, p->lda, g.m, Bcs, g.k, g.bc, g.k, C + g.n, p->ldc, 1);
+    return slivers(sliver_job<E, float, float>(Bt, p->ldb, g.n, Acs, g.k, g.br, g.k, Crow, 1, p->ldc), &cols, x, s);
 }
 
 int launch_skinny_f64(const double *A, int64_t lda, const double *Bt, int64_t ldb, double *C, int64_t ldc,
                       int64_t M, int64_t N, int64_t K, hipStream_t s) {
-    int st = sliver<double, double, double>(A, lda, M, Bt, ldb, N, K, C, ldc, 1, nullptr, s);
-    if (st) return st;
-    ABFT_LAUNCHED();
-    return ABFT_OK;
+    return slivers(sliver_job<double, double, double>(A, lda, M, Bt, ldb, N, K, C, ldc, 1),
+                   (const SliverJob<double, double, double> *)nullptr, sliver_extra(nullptr, false), s);
 }
 
 int launch_gemm_f64(const double *A, int64_t lda, const double *Bt, int64_t ldb, double *C, int64_t ldc, int64_t M,
@@ -263,10 +282,8 @@ int launch_gemm_f64(const double *A, int64_t lda, const double *Bt, int64_t ldb,
 
 int launch_skinny_f32(const float *A, int64_t lda, const float *Bt, int64_t ldb, float *C, int64_t ldc,
                       int64_t M, int64_t N, int64_t K, hipStream_t s) {
-    int st = sliver<float, float, float>(A, lda, M, Bt, ldb, N, K, C, ldc, 1, nullptr, s);
-    if (st) return st;
-    ABFT_LAUNCHED();
-    return ABFT_OK;
+    return slivers(sliver_job<float, float, float>(A, lda, M, Bt, ldb, N, K, C, ldc, 1),
+                   (const SliverJob<float, float, float> *)nullptr, sliver_extra(nullptr, false), s);
 }
 
 int launch_gemm_f32(const float *A, int64_t lda, const float *Bt, int64_t ldb, float *C, int64_t ldc, int64_t M,
@@ -359,20 +376,20 @@ __global__ void k_store_tag(uint64_t *dst, uint64_t v) { *dst = v; }
 
 static int product_with_extras(const abft_problem *p, const Geom &g, const void *A_f, const void *B_f, void *C_f,
                                bool plain, void *ws, const float *Acs, const float *Bcs, const int *scale,
-                               EpiArgs *e, hipStream_t s) {
+                               EpiArgs *e, TagStore *tag, hipStream_t s) {
     switch (p->dtype) {
     case ABFT_F64:
         return protected_product<double>(p, g, (const double *)A_f, (const double *)B_f, (double *)C_f, plain, s, 0,
-                                         -1, false, e);
+                                         -1, false, e, tag);
     case ABFT_F32:
         return protected_product<float>(p, g, (const float *)A_f, (const float *)B_f, (float *)C_f, plain, s, 0, -1,
-                                        false, e);
+                                        false, e, tag);
     case ABFT_BF16:
         return protected_product_lowp<Bf16Ops, Bf16Ops>(p, g, (const uint16_t *)A_f, (const uint16_t *)B_f,
-                                                        (float *)C_f, Acs, Bcs, nullptr, plain, s, e);
+                                                        (float *)C_f, Acs, Bcs, nullptr, plain, s, e, tag);
     case ABFT_FP8_E4M3:
         return protected_product_lowp<Fp8Ops, Fp8x64Ops>(p, g, (const uint8_t *)A_f, (const uint8_t *)B_f,
-                                                         (float *)C_f, Acs, Bcs, scale, plain, s, e);
+                                                         (float *)C_f, Acs, Bcs, scale, plain, s, e, tag);
     default:
         return ABFT_E_UNSUPPORTED;
     }
@@ -399,17 +416,13 @@ int launch_gemm(const abft_problem *p, const void *A_f, const void *B_f, void *C
     const float *Acs = (lowp && ws) ? (const float *)(wsc + L.acs) : nullptr;
     const float *Bcs = (lowp && ws) ? (const float *)(wsc + L.bcs) : nullptr;
     const int *scale = (p->dtype == ABFT_FP8_E4M3 && ws) ? (const int *)(wsc + L.scale) : nullptr;
-    int st = product_with_extras(p, g, A_f, B_f, C_f, plain, ws, Acs, Bcs, scale, (fault || fused) ? &e : nullptr, s);
+    // ws records who owns the fused partials now: this product (fused) or nobody
+    TagStore tag{ws ? (uint64_t *)((char *)ws + L.fused_tag) : nullptr, p, C_f, fused, &e};
+    int st = product_with_extras(p, g, A_f, B_f, C_f, plain, ws, Acs, Bcs, scale, (fault || fused) ? &e : nullptr,
+                                 ws ? &tag : nullptr, s);
     if (st) return st;
-    if (ws) {
-        // record in ws who owns the fused partials now: this product (fused) or nobody
-        uint64_t key = 0;
-        if (fused) {
-            int64_t tm = 0, tn = 0;
-            key = fused_key(p, C_f, &tm, &tn);
-            if (tm != e.tiles_m || tn != e.tiles_n) key = 0;   // a grid the fused verification would not read
-        }
-        k_store_tag<<<1, 1, 0, s>>>((uint64_t *)((char *)ws + L.fused_tag), key);
+    if (tag.dst) {                                   // no carried blocks' launch stored it
+        k_store_tag<<<1, 1, 0, s>>>(tag.dst, tag.key());
         ABFT_LAUNCHED();
     }
     return ABFT_OK;

@@ -5,9 +5,17 @@
 //   carried column block C_f[i, n + c] = sum_l A_f[i, l] (B C_R)[l, c]     (i < rows, c < bc)
 // Both have the form out[u, s] = sum_l X[u, l] Y[s, l] with many rows u (a
 // whole operand, streamed once from HBM) and few rows s (the checksum rows,
-// L2-resident).  One wave owns one u at a time; lanes stride k with 16-byte
+// L2-resident).  A wave owns one u, or several; lanes stride k with 16-byte
 // loads; the few partial sums are folded with wavefront shuffles.
+//
+// HBM-bound.  The chunks of the next step are requested before the current
+// ones are summed: with a step's loads, wait and sums in turn the rate stays
+// at 5 TB/s however many rows share a wave, with the next step in flight it is
+// 6.5 (2.1 GB binary64 operand against two rows, four rows per wave: 401 us
+// and 330).
 #pragma once
+
+#include <type_traits>
 
 #include "common.h"
 
@@ -26,172 +34,263 @@ template <> __device__ inline void store_out<float>(float *p, double v, bool acc
 }
 
 // X: U rows of type TX (ldx); Y: R rows of type TY (ldy), R <= kSliverR per launch.
-// out[u*ou + s*os] = scale * sum_l X[u,l] Y[s,l], scale = 2^-(e[0] + e[1]) when
-// the device scale exponents e are given (FP8), else 1.  K is a multiple of
-// both vector widths.
-template <typename TX, typename TY, typename TC>
-__global__ __launch_bounds__(kSliverThreads) void k_sliver(const TX *__restrict__ X, int64_t ldx, int64_t U,
-                                                          const TY *__restrict__ Y, int64_t ldy, int R, int64_t K,
-                                                          TC *__restrict__ out, int64_t ou, int64_t os,
-                                                          const int *__restrict__ scale_exp, int accumulate) {
-    const double scale = scale_exp ? ldexp(1.0, -(scale_exp[0] + scale_exp[1])) : 1.0;
-    constexpr int VX = vec16<TX>::N, VY = vec16<TY>::N;
-    constexpr int V = VX > VY ? VX : VY;             // k per lane per step
-    const int lane = threadIdx.x % 64;
-    const int64_t wave = ((int64_t)blockIdx.x * kSliverThreads + threadIdx.x) / 64;
-    const int64_t nwaves = (int64_t)gridDim.x * kSliverThreads / 64;
-    constexpr int UNR = V >= 16 ? 1 : (V >= 8 ? 2 : 4);   // 16-byte loads in flight per lane and operand row
-    for (int64_t u = wave; u < U; u += nwaves) {
-        double acc[kSliverR];
-#pragma unroll
-        for (int s = 0; s < kSliverR; ++s) acc[s] = 0.0;
-        const TX *xr = X + u * ldx;
-        int64_t k0 = (int64_t)lane * V;
-        for (; k0 + (UNR - 1) * 64 * V < K; k0 += UNR * 64 * V) {
-            double xv[UNR][V];
-#pragma unroll
-            for (int w = 0; w < UNR; ++w)
-#pragma unroll
-                for (int q = 0; q < V; q += VX) vec16<TX>::load(xr + k0 + w * 64 * V + q, xv[w] + q);
-#pragma unroll
-            for (int s = 0; s < kSliverR; ++s) {
-                if (s < R) {
-                    double yv[UNR][V];
-#pragma unroll
-                    for (int w = 0; w < UNR; ++w)
-#pragma unroll
-                        for (int q = 0; q < V; q += VY) vec16<TY>::load(Y + s * ldy + k0 + w * 64 * V + q, yv[w] + q);
-#pragma unroll
-                    for (int w = 0; w < UNR; ++w)
-#pragma unroll
-                        for (int q = 0; q < V; ++q) acc[s] = fma(xv[w][q], yv[w][q], acc[s]);
-                }
-            }
-        }
-        for (; k0 < K; k0 += 64 * V) {
-            double xv[V];
-#pragma unroll
-            for (int q = 0; q < V; q += VX) vec16<TX>::load(xr + k0 + q, xv + q);
-#pragma unroll
-            for (int s = 0; s < kSliverR; ++s) {
-                if (s < R) {
-                    double yv[V];
-#pragma unroll
-                    for (int q = 0; q < V; q += VY) vec16<TY>::load(Y + s * ldy + k0 + q, yv + q);
-#pragma unroll
-                    for (int q = 0; q < V; ++q) acc[s] = fma(xv[q], yv[q], acc[s]);
-                }
-            }
-        }
-#pragma unroll
-        for (int s = 0; s < kSliverR; ++s) {
-            double v = acc[s];
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-            if (lane == 0 && s < R) store_out<TC>(out + u * ou + s * os, scale * v, accumulate != 0);
-        }
-    }
+// out[u*ou + s*os] = scale * sum_l X[u,l] Y[s,l].  K is a multiple of both vector widths.
+template <typename TX, typename TY, typename TC> struct SliverJob {
+    const TX *X;
+    int64_t ldx, U;
+    const TY *Y;
+    int64_t ldy;
+    int R;
+    int64_t K;
+    TC *out;
+    int64_t ou, os;
+    unsigned blocks;
+};
+
+// What else one launch may do: the corner of binary32 checksum rows,
+// C_f[m + r, n + c] = scale * sum_l Yr[r, l] Yc[c, l], a block per entry, and the
+// owner tag of the fused partial sums.
+struct SliverExtra {
+    const float *Yr, *Yc;     // null: no corner
+    int64_t K, nc;            // columns of the corner
+    float *out;
+    int64_t ldo;
+    unsigned blocks;
+    uint64_t *tag;            // null: none
+    uint64_t key;
+    const int *scale_exp;     // FP8 scale exponents: scale = 2^-(e[0] + e[1]); null: 1
+    int accumulate;
+};
+inline SliverExtra sliver_extra(const int *scale_exp, bool accumulate) {
+    SliverExtra x{};
+    x.scale_exp = scale_exp;
+    x.accumulate = accumulate ? 1 : 0;
+    return x;
 }
 
-// One checksum row (R = 1): a wave takes NR rows of X together, so that each
-// chunk of Y is read once for NR rows and NR 16-byte loads of X are in flight
-// per lane (kept raw until summed).  Per row the same sums in the same order
-// as k_sliver: each lane over its chunks in increasing k, then the butterfly.
-template <typename TX, typename TY, typename TC, int NR, int UK>
-__global__ __launch_bounds__(kSliverThreads) void k_sliver1(const TX *__restrict__ X, int64_t ldx, int64_t U,
-                                                           const TY *__restrict__ Y, int64_t K, TC *__restrict__ out,
-                                                           int64_t ou, const int *__restrict__ scale_exp,
-                                                           int accumulate) {
-    const double scale = scale_exp ? ldexp(1.0, -(scale_exp[0] + scale_exp[1])) : 1.0;
+// NR rows of X per wave, NY >= R rows of Y (rows at and past R repeat the last,
+// and are not stored), UK chunks of k per lane in a step.
+template <typename TX, typename TY, typename TC, int NR, int NY, int UK, bool NT>
+__device__ __attribute__((always_inline)) inline void sliver_rows(const SliverJob<TX, TY, TC> &j, double scale,
+                                                                  bool accumulate, int64_t block) {
     constexpr int VX = vec16<TX>::N, VY = vec16<TY>::N;
-    constexpr int V = VX > VY ? VX : VY;             // k per lane per step
+    constexpr int V = VX > VY ? VX : VY;             // k per lane per chunk
+    constexpr bool PFY = NY * (V / VY) <= 4;         // Y's chunks requested ahead too (as registers allow)
     const int lane = threadIdx.x % 64;
-    const int64_t wave = ((int64_t)blockIdx.x * kSliverThreads + threadIdx.x) / 64;
-    const int64_t nwaves = (int64_t)gridDim.x * kSliverThreads / 64;
-    for (int64_t u0 = wave * NR; u0 < U; u0 += nwaves * NR) {
-        double acc[NR];
+    const int64_t wave = block * (kSliverThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int64_t nwaves = (int64_t)j.blocks * (kSliverThreads / 64);
+    for (int64_t u0 = wave * NR; u0 < j.U; u0 += nwaves * NR) {
+        double acc[NR][NY];
         const TX *xr[NR];
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
-            acc[r] = 0.0;
-            xr[r] = X + min(u0 + r, U - 1) * ldx;      // rows past U re-read the last (not stored)
-        }
-        // UK chunks of k per lane in flight (a chunk at or past K is clamped to
-        // the lane's first and not summed)
-        for (int64_t k0 = (int64_t)lane * V; k0 < K; k0 += UK * 64 * V) {
-            v4u32 xw[UK][NR][V / VX], yw[UK][V / VY];
 #pragma unroll
-            for (int c = 0; c < UK; ++c) {
-                const int64_t kc = k0 + c * 64 * V < K ? k0 + c * 64 * V : k0;
+            for (int y = 0; y < NY; ++y) acc[r][y] = 0.0;
+            xr[r] = j.X + min(u0 + r, j.U - 1) * j.ldx;  // rows past U re-read the last (not stored)
+        }
+        // a chunk at or past K is clamped to the step's first and not summed
+        auto at = [&](int64_t k0, int c) { return k0 + c * 64 * V < j.K ? k0 + c * 64 * V : k0; };
+        auto get_x = [&](v4u32 (&x)[UK][NR][V / VX], int64_t k0) {
+#pragma unroll
+            for (int c = 0; c < UK; ++c)
 #pragma unroll
                 for (int r = 0; r < NR; ++r)
 #pragma unroll
-                    for (int q = 0; q < V / VX; ++q) xw[c][r][q] = *(const v4u32 *)(xr[r] + kc + q * VX);
+                    for (int q = 0; q < V / VX; ++q) x[c][r][q] = load_raw<NT, v4u32>(xr[r] + at(k0, c) + q * VX);
+        };
+        auto get_y = [&](v4u32 (&yw)[UK][NY][V / VY], int64_t k0) {
 #pragma unroll
-                for (int q = 0; q < V / VY; ++q) yw[c][q] = *(const v4u32 *)(Y + kc + q * VY);
+            for (int c = 0; c < UK; ++c)
+#pragma unroll
+                for (int y = 0; y < NY; ++y)
+#pragma unroll
+                    for (int q = 0; q < V / VY; ++q)
+                        yw[c][y][q] = *(const v4u32 *)(j.Y + (int64_t)min(y, j.R - 1) * j.ldy + at(k0, c) + q * VY);
+        };
+        v4u32 nx[UK][NR][V / VX], ny[UK][NY][V / VY];
+        int64_t k0 = (int64_t)lane * V;
+        if (k0 < j.K) {
+            get_x(nx, k0);
+            if constexpr (PFY) get_y(ny, k0);
+        }
+        for (; k0 < j.K; k0 += UK * 64 * V) {
+            v4u32 xw[UK][NR][V / VX], yw[UK][NY][V / VY];
+#pragma unroll
+            for (int c = 0; c < UK; ++c) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+#pragma unroll
+                    for (int q = 0; q < V / VX; ++q) xw[c][r][q] = nx[c][r][q];
+                if constexpr (PFY) {
+#pragma unroll
+                    for (int y = 0; y < NY; ++y)
+#pragma unroll
+                        for (int q = 0; q < V / VY; ++q) yw[c][y][q] = ny[c][y][q];
+                }
+            }
+            if constexpr (!PFY) get_y(yw, k0);
+            if (k0 + UK * 64 * V < j.K) {
+                get_x(nx, k0 + UK * 64 * V);
+                if constexpr (PFY) get_y(ny, k0 + UK * 64 * V);
             }
 #pragma unroll
             for (int c = 0; c < UK; ++c) {
-                if (k0 + c * 64 * V >= K) break;
-                double yv[V];
+                if (k0 + c * 64 * V >= j.K) break;
+                double xv[NR][V];
 #pragma unroll
-                for (int q = 0; q < V / VY; ++q) vec16<TY>::widen(yw[c][q], yv + q * VY);
+                for (int r = 0; r < NR; ++r)
 #pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    double xv[V];
+                    for (int q = 0; q < V / VX; ++q) vec16<TX>::widen(xw[c][r][q], xv[r] + q * VX);
 #pragma unroll
-                    for (int q = 0; q < V / VX; ++q) vec16<TX>::widen(xw[c][r][q], xv + q * VX);
+                for (int y = 0; y < NY; ++y) {
+                    double yv[V];
 #pragma unroll
-                    for (int q = 0; q < V; ++q) acc[r] = fma(xv[q], yv[q], acc[r]);
+                    for (int q = 0; q < V / VY; ++q) vec16<TY>::widen(yw[c][y][q], yv + q * VY);
+#pragma unroll
+                    for (int r = 0; r < NR; ++r)
+#pragma unroll
+                        for (int q = 0; q < V; ++q) acc[r][y] = fma(xv[r][q], yv[q], acc[r][y]);
                 }
             }
         }
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            double v = acc[r];
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-            if (lane == 0 && u0 + r < U) store_out<TC>(out + (u0 + r) * ou, scale * v, accumulate != 0);
-        }
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+            for (int y = 0; y < NY; ++y) {
+                double v = acc[r][y];
+                for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+                if (lane == 0 && u0 + r < j.U && y < j.R)
+                    store_out<TC>(j.out + (u0 + r) * j.ou + y * j.os, scale * v, accumulate);
+            }
     }
 }
-// k_sliver1 serves one checksum row over enough operand rows to fill the device.
-inline bool sliver_multirow(int64_t R, int64_t U) { return R == 1 && U >= 16384; }
-constexpr int kSliverRows = 4;        // rows of X per wave in k_sliver1
-constexpr int kSliverChunks = 2;      // chunks of k per lane in flight in k_sliver1
 
-template <typename TX, typename TY, typename TC>
-inline int sliver(const TX *X, int64_t ldx, int64_t U, const TY *Y, int64_t ldy, int64_t R, int64_t K, TC *out,
-                  int64_t ou, int64_t os, const int *scale_exp, hipStream_t s, bool accumulate = false) {
-    const int64_t waves_per_block = kSliverThreads / 64;
-    if (sliver_multirow(R, U)) {
-        const int64_t waves = (U + kSliverRows - 1) / kSliverRows;
-        const unsigned blocks = (unsigned)std::min<int64_t>((waves + waves_per_block - 1) / waves_per_block, 4096);
-        k_sliver1<TX, TY, TC, kSliverRows, kSliverChunks><<<blocks, kSliverThreads, 0, s>>>(X, ldx, U, Y, K, out, ou, scale_exp,
-                                                                            accumulate ? 1 : 0);
-        ABFT_LAUNCHED();
-        return ABFT_OK;
+__device__ inline void sliver_corner(const SliverExtra &x, double scale, int64_t e) {
+    __shared__ double sh[kSliverThreads / 64];
+    const int64_t r = e / x.nc, c = e - r * x.nc;
+    const float *a = x.Yr + r * x.K, *b = x.Yc + c * x.K;
+    double acc = 0.0;
+    for (int64_t l = (int64_t)threadIdx.x * 4; l < x.K; l += kSliverThreads * 4) {
+        double av[4], bv[4];
+        vec16<float>::load(a + l, av);
+        vec16<float>::load(b + l, bv);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc = fma(av[q], bv[q], acc);
     }
-    unsigned blocks = (unsigned)std::min<int64_t>((U + waves_per_block - 1) / waves_per_block, 4096);
-    for (int64_t r0 = 0; r0 < R; r0 += kSliverR) {
-        int rr = (int)std::min<int64_t>(kSliverR, R - r0);
-        k_sliver<TX, TY, TC><<<blocks, kSliverThreads, 0, s>>>(X, ldx, U, Y + r0 * ldy, ldy, rr, K, out + r0 * os, ou,
-                                                               os, scale_exp, accumulate ? 1 : 0);
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if (threadIdx.x % 64 == 0) sh[threadIdx.x / 64] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < kSliverThreads / 64; ++q) acc += sh[q];
+        x.out[r * x.ldo + c] = (float)(scale * acc);
+    }
+}
+
+// One or two jobs (blocks [0, a.blocks), then b's), then the extras.
+template <typename TX, typename TY, typename TC, int NR, int NY, int UK, bool NT>
+__device__ __attribute__((always_inline)) inline void sliver_launch(const SliverJob<TX, TY, TC> &a,
+                                                                    const SliverJob<TX, TY, TC> &b,
+                                                                    const SliverExtra &x) {
+    const double scale = x.scale_exp ? ldexp(1.0, -(x.scale_exp[0] + x.scale_exp[1])) : 1.0;
+    if (x.tag && blockIdx.x == 0 && threadIdx.x == 0) *x.tag = x.key;
+    const unsigned blk = blockIdx.x;
+    if (blk >= a.blocks + b.blocks) {
+        sliver_corner(x, scale, blk - a.blocks - b.blocks);
+        return;
+    }
+    const bool first = blk < a.blocks;
+    sliver_rows<TX, TY, TC, NR, NY, UK, NT>(first ? a : b, scale, x.accumulate != 0, first ? blk : blk - a.blocks);
+}
+template <typename TX, typename TY, typename TC, int NY, bool NT>
+__global__ __launch_bounds__(kSliverThreads) void k_sliver(SliverJob<TX, TY, TC> a, SliverJob<TX, TY, TC> b,
+                                                          SliverExtra x) {
+    constexpr int V = vec16<TX>::N > vec16<TY>::N ? vec16<TX>::N : vec16<TY>::N;
+    // chunks of k per lane in a step, fewer where more rows of Y hold registers
+    constexpr int UK = V >= 16 ? 1 : (V >= 8 ? (NY > 2 ? 1 : 2) : (NY > 2 ? 1 : 4 / NY));
+    sliver_launch<TX, TY, TC, 1, NY, UK, NT>(a, b, x);
+}
+// Few checksum rows over enough operand rows to fill the device: a wave takes
+// four operand rows, so each chunk of Y is read once for the four.  Per row the
+// same sums in the same order as k_sliver.
+constexpr int kSliverRows = 4;
+template <typename TX, typename TY, typename TC, int NY, bool NT>
+__global__ __launch_bounds__(kSliverThreads) void k_sliver1(SliverJob<TX, TY, TC> a, SliverJob<TX, TY, TC> b,
+                                                           SliverExtra x) {
+    sliver_launch<TX, TY, TC, kSliverRows, NY, 1, NT>(a, b, x);
+}
+inline bool sliver_multirow(int64_t R, int64_t U) { return R <= 2 && U >= 16384; }
+
+// One or two skinny products (b null: one) and the extras, which go with the last launch.
+template <typename TX, typename TY, typename TC>
+inline int slivers(SliverJob<TX, TY, TC> a, const SliverJob<TX, TY, TC> *b, const SliverExtra &x, hipStream_t s) {
+    typedef SliverJob<TX, TY, TC> Job;
+    SliverExtra plain = sliver_extra(x.scale_exp, x.accumulate != 0);
+    // at most kSliverR checksum rows of one job per launch
+    auto run = [&](Job u, Job v, bool with_v, const SliverExtra &e) {
+        if (!with_v) { v = u; v.blocks = 0; }
+        const int64_t per_block = kSliverThreads / 64;
+        const bool multi = sliver_multirow(u.R, u.U);
+        auto blocks = [&](const Job &j) {
+            const int64_t waves = multi ? (j.U + kSliverRows - 1) / kSliverRows : j.U;
+            return (unsigned)std::min<int64_t>((waves + per_block - 1) / per_block, 4096);
+        };
+        u.blocks = blocks(u);
+        if (with_v) v.blocks = blocks(v);
+        const int R = with_v ? std::max(u.R, v.R) : u.R;
+        const bool nt = streams(std::max(u.U, with_v ? v.U : 0) * u.K * (int64_t)sizeof(TX));
+        const unsigned grid = u.blocks + v.blocks + e.blocks;
+        auto go = [&](auto ny, auto st) {
+            constexpr int NY = decltype(ny)::value;
+            constexpr bool NT = decltype(st)::value;
+            if (multi) {
+                if constexpr (NY <= 2) k_sliver1<TX, TY, TC, NY, NT><<<grid, kSliverThreads, 0, s>>>(u, v, e);
+            } else {
+                k_sliver<TX, TY, TC, NY, NT><<<grid, kSliverThreads, 0, s>>>(u, v, e);
+            }
+        };
+        auto by_ny = [&](auto st) {
+            if (R == 1) go(std::integral_constant<int, 1>{}, st);
+            else if (R == 2) go(std::integral_constant<int, 2>{}, st);
+            else if (R <= 4) go(std::integral_constant<int, 4>{}, st);
+            else go(std::integral_constant<int, 8>{}, st);
+        };
+        nt ? by_ny(std::true_type{}) : by_ny(std::false_type{});
+    };
+    auto piece = [](Job j, int r0) {
+        j.Y += r0 * j.ldy;
+        j.out += r0 * j.os;
+        j.R = std::min(j.R - r0, kSliverR);
+        return j;
+    };
+    const bool one = b && a.R == b->R && a.R <= kSliverR && sliver_multirow(a.R, a.U) == sliver_multirow(b->R, b->U);
+    if (one) {
+        run(a, *b, true, x);
+    } else {
+        for (int r = 0; r < a.R; r += kSliverR) run(piece(a, r), a, false, !b && r + kSliverR >= a.R ? x : plain);
+        for (int r = 0; b && r < b->R; r += kSliverR) run(piece(*b, r), a, false, r + kSliverR >= b->R ? x : plain);
     }
     ABFT_LAUNCHED();
     return ABFT_OK;
 }
 
+template <typename TX, typename TY, typename TC>
+inline SliverJob<TX, TY, TC> sliver_job(const TX *X, int64_t ldx, int64_t U, const TY *Y, int64_t ldy, int64_t R, int64_t K,
+                                        TC *out, int64_t ou, int64_t os) {
+    return SliverJob<TX, TY, TC>{X, ldx, U, Y, ldy, (int)R, K, out, ou, os, 0};
+}
+
 // Carried row block: C_f[m + r, 0:N) = sum_l Acs[r, l] Bt[j, l] (checksum rows Acs, br x K; the
 // operands may start at a k offset, K is the panel depth).
-template <typename TA, typename TB, typename TC>
-inline int launch_sliver_rows(const Geom &g, const TA *Acs, int64_t ldacs, const TB *Bt, int64_t ldb, TC *C,
-                              int64_t ldc, int64_t K, bool accumulate, hipStream_t s) {
-    return sliver<TB, TA, TC>(Bt, ldb, g.N, Acs, ldacs, g.br, K, C + g.m * ldc, 1, ldc, nullptr, s, accumulate);
+template <typename E>
+inline SliverJob<E, E, E> sliver_carried_rows(const Geom &g, const E *Acs, int64_t ldacs, const E *Bt, int64_t ldb, E *C,
+                                              int64_t ldc, int64_t K) {
+    return sliver_job<E, E, E>(Bt, ldb, g.N, Acs, ldacs, g.br, K, C + g.m * ldc, 1, ldc);
 }
 // Carried column block: C_f[0:rows, n + c) = sum_l A[i, l] Bcs[c, l] (checksum columns Bcs, bc x K).
-template <typename TA, typename TB, typename TC>
-inline int launch_sliver_cols(const Geom &g, int64_t rows, const TA *A, int64_t lda, const TB *Bcs, int64_t ldbcs,
-                              TC *C, int64_t ldc, int64_t K, bool accumulate, hipStream_t s) {
-    return sliver<TA, TB, TC>(A, lda, rows, Bcs, ldbcs, g.bc, K, C + g.n, ldc, 1, nullptr, s, accumulate);
+template <typename E>
+inline SliverJob<E, E, E> sliver_carried_cols(const Geom &g, int64_t rows, const E *A, int64_t lda, const E *Bcs,
+                                              int64_t ldbcs, E *C, int64_t ldc, int64_t K) {
+    return sliver_job<E, E, E>(A, lda, rows, Bcs, ldbcs, g.bc, K, C + g.n, ldc, 1);
 }
 
 }  // namespace abft
