@@ -15,15 +15,22 @@ void set_hip_error(hipError_t e) { g_last_hip_error = (int)e; }
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-int64_t group_partitions(int64_t G, int64_t b, int64_t cols) {
-    // Enough independent sums to fill 256 CUs with ~2K threads each; each
-    // partition sums a contiguous run of groups in ascending order.
-    const int64_t target = int64_t(1) << 19;
-    int64_t rel = b * cols;
-    int64_t P = (target + rel - 1) / rel;
-    if (P > G) P = G;
-    if (P < 1) P = 1;
-    return P;
+VcolSplit vcol_split(const Geom &g, int V) {
+    VcolSplit c;
+    const int64_t nv = (g.N + V - 1) / V;
+    c.strips = (nv + 63) / 64;
+    // whole residues per lane where few groups or enough residues make it short, else partitions for about
+    // eight blocks per CU, of at least four rows per wave; the partial sums stay within 2^19 values (or a
+    // residue's worth each)
+    const int64_t want = 2048 / (c.strips * g.br);
+    c.direct = g.Gr <= 16 || want < 2;
+    c.P = 1;
+    c.chunk = g.Gr;
+    if (!c.direct) {
+        c.chunk = std::min(g.Gr, std::max<int64_t>((g.Gr + want - 1) / want, 16));
+        c.P = (g.Gr + c.chunk - 1) / c.chunk;
+    }
+    return c;
 }
 
 EncSplit enc_split(int64_t R, int64_t b, int64_t k, int V) {
@@ -72,11 +79,12 @@ WsLayout ws_layout(const abft_problem *p) {
     L.amax = take(p->dtype == ABFT_FP8_E4M3 ? sizeof(float) * 2 * kAmaxBlocks : 8);
     // partial sums: encode A (2 stats), encode B (2 stats), verify columns (1, in A's)
     const EncSplit ea = enc_split(g.m, g.br, g.k, enc_vec(p->dtype)), eb = enc_split(g.n, g.bc, g.k, enc_vec(p->dtype));
-    int64_t pc = std::max(group_partitions(g.Gr, g.br, g.N), group_partitions(g.Gr, g.br, (g.N + 1) / 2));
-    pc = std::max(pc, group_partitions(g.Gr, g.br, (g.N + 3) / 4));
     size_t need = 0;
     if (!ea.direct) need = (size_t)(ea.P * g.br * g.k * 2);
-    if (pc > 1) need = std::max(need, (size_t)(pc * g.br * g.N));
+    for (int V : {1, 2, 4}) {
+        const VcolSplit sp = vcol_split(g, V);
+        if (!sp.direct) need = std::max(need, (size_t)(sp.P * g.br * g.N));
+    }
     L.partial_bytes = sizeof(double) * need;
     L.partial = take(L.partial_bytes > 0 ? L.partial_bytes : 8);
     L.partial_b = take(eb.direct ? 8 : sizeof(double) * (size_t)(eb.P * g.bc * g.k * 2));

@@ -272,8 +272,14 @@ constexpr int64_t kEncRereadBytes = int64_t(48) << 20;
 // Blocks per operand of the FP8 amax pass: eight per CU.
 constexpr int64_t kAmaxBlocks = 2048;
 
-// Number of partitions used for the row-group sums of a (G groups, b residues, cols) sum.
-int64_t group_partitions(int64_t G, int64_t b, int64_t cols);
+// How the verification sums the columns of C_f (M x N, V columns per lane):
+// each lane whole residues, or a block one of P partitions of a residue over a
+// strip of 64 V columns.
+struct VcolSplit {
+    bool direct;
+    int64_t strips, P, chunk;
+};
+VcolSplit vcol_split(const Geom &g, int V);
 
 // ------------------------------------------------------------------ error plumbing
 void set_hip_error(hipError_t e);

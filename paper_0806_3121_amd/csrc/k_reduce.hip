@@ -41,9 +41,12 @@ __device__ inline void fold_block(double ratio, unsigned long long excl, double 
         unsigned long long e = s_e[0];
         for (int q = 1; q < kThreads / kWave; ++q) { r = fmax(r, s_r[q]); e += s_e[q]; }
         if (r > 0) {
+            // ordering of non-negative doubles = ordering of their bits; the maximum only grows, so a block
+            // that cannot raise it leaves it alone (thousands of blocks' atomics on one address took 40 us)
             unsigned long long bits;
             __builtin_memcpy(&bits, &r, 8);
-            atomicMax((unsigned long long *)rep_ratio, bits);   // ordering of non-negative doubles = ordering of their bits
+            unsigned long long *dst = (unsigned long long *)rep_ratio;
+            if (bits > __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(dst, bits);
         }
         if (e) atomicAdd((unsigned long long *)rep_excl, e);
     }
@@ -64,19 +67,18 @@ __device__ inline double record(abft_report *rep, bool col, int64_t a, int64_t b
     return 0.0;
 }
 
-__global__ void k_report_init(abft_report *rep) {
+__device__ inline void clear_report(abft_report *rep) {
     uint64_t *w = (uint64_t *)rep;
     const int nw = sizeof(abft_report) / 8;
     for (int q = threadIdx.x; q < nw; q += blockDim.x) w[q] = 0;
 }
+__global__ void k_report_init(abft_report *rep) { clear_report(rep); }
 
 // Report of a fused verification: cleared, with status ABFT_E_STALE when the
 // owner tag in ws does not name this problem and C_f (the verify kernels then
 // record nothing).
 __global__ void k_report_init_tag(abft_report *rep, const uint64_t *tag, uint64_t key) {
-    uint64_t *w = (uint64_t *)rep;
-    const int nw = sizeof(abft_report) / 8;
-    for (int q = threadIdx.x; q < nw; q += blockDim.x) w[q] = 0;
+    clear_report(rep);
     __syncthreads();
     if (threadIdx.x == 0 && *tag != key) rep->status = ABFT_E_STALE;
 }
@@ -1054,18 +1056,29 @@ template <typename T, int V> __device__ inline void load_c(const T *p, double *v
 // last vector of a row stays inside the row's ldc elements; columns >= N are
 // read but not used.
 template <typename T, int V>
-__global__ __launch_bounds__(kThreads) void k_vcol_direct(const T *C, VerifyArgs a) {
+__device__ inline void vcol_direct(const VerifyArgs &a, const T *C, int64_t blk, int64_t nblk) {
     const int64_t nv = (a.N + V - 1) / V, total = a.br * nv;
     double ratio = 0.0;
     unsigned long long excl = 0;
-    for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < total; t += (int64_t)gridDim.x * kThreads) {
+    for (int64_t t = blk * kThreads + threadIdx.x; t < total; t += nblk * kThreads) {
         int64_t r = t / nv, j0 = (t - r * nv) * V;
         const T *p = C + r * a.ldc + j0;
         double s[V], v[V];
 #pragma unroll
         for (int q = 0; q < V; ++q) s[q] = 0.0;
-        for (int64_t g = 0; g < a.Gr; ++g) {
-            load_c<T, V>(p + g * a.br * a.ldc, v);
+        const int64_t rs = a.br * a.ldc;
+        int64_t g = 0;
+        for (; g + 3 < a.Gr; g += 4) {                 // four rows requested together
+            double w[4][V];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) load_c<T, V>(p + (g + u) * rs, w[u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int q = 0; q < V; ++q) s[q] += w[u][q];
+        }
+        for (; g < a.Gr; ++g) {
+            load_c<T, V>(p + g * rs, v);
 #pragma unroll
             for (int q = 0; q < V; ++q) s[q] += v[q];
         }
@@ -1076,39 +1089,62 @@ __global__ __launch_bounds__(kThreads) void k_vcol_direct(const T *C, VerifyArgs
     fold_block(ratio, excl, &a.rep->max_ratio_c, &a.rep->n_excl_c);
 }
 
+// Partitioned: a block sums one partition of one residue over a strip of 64
+// vectors, its four waves taking the groups in turn (four rows requested
+// together) and adding up through LDS.  The first block also clears the
+// report: nothing is recorded before the next launch.
 template <typename T, int V>
-__global__ __launch_bounds__(kThreads) void k_vcol_partial(const T *C, VerifyArgs a, int64_t P, int64_t chunk, double *part) {
-    const int64_t nv = (a.N + V - 1) / V, rel = a.br * a.N, total = P * a.br * nv;
-    for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < total; t += (int64_t)gridDim.x * kThreads) {
-        int64_t p = t / (a.br * nv), q = t - p * (a.br * nv);
-        int64_t r = q / nv, j0 = (q - r * nv) * V;
-        int64_t g0 = p * chunk, g1 = min(a.Gr, g0 + chunk);
-        const T *src = C + r * a.ldc + j0;
-        double s[V], v[V];
+__global__ __launch_bounds__(kThreads) void k_vcol_partial(const T *C, VerifyArgs a, VcolSplit sp, double *part) {
+    constexpr int NW = kThreads / kWave;
+    __shared__ double sh[NW][kWave * V];
+    if (blockIdx.x == 0) clear_report(a.rep);
+    const int64_t strip = blockIdx.x % sp.strips, pr = blockIdx.x / sp.strips, r = pr % a.br, p = pr / a.br;
+    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+    const int64_t j0 = (strip * kWave + lane) * V;
+    const bool ok = j0 < a.N;
+    const int64_t g1 = min(a.Gr, (p + 1) * sp.chunk), rs = a.br * a.ldc;
+    const T *src = C + r * a.ldc + (ok ? j0 : 0);
+    double s[V] = {}, v[4][V];
+    int64_t g = p * sp.chunk + w;
+    for (; g + 3 * NW < g1; g += 4 * NW) {
 #pragma unroll
-        for (int e = 0; e < V; ++e) s[e] = 0.0;
-        for (int64_t g = g0; g < g1; ++g) {
-            load_c<T, V>(src + g * a.br * a.ldc, v);
+        for (int u = 0; u < 4; ++u) load_c<T, V>(src + (g + u * NW) * rs, v[u]);
 #pragma unroll
-            for (int e = 0; e < V; ++e) s[e] += v[e];
-        }
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int e = 0; e < V; ++e)
-            if (j0 + e < a.N) part[p * rel + r * a.N + j0 + e] = s[e];
+            for (int e = 0; e < V; ++e) s[e] += v[u][e];
+    }
+    for (; g < g1; g += NW) {
+        load_c<T, V>(src + g * rs, v[0]);
+#pragma unroll
+        for (int e = 0; e < V; ++e) s[e] += v[0][e];
+    }
+#pragma unroll
+    for (int e = 0; e < V; ++e) sh[w][e * kWave + lane] = s[e];
+    __syncthreads();
+    for (int t = threadIdx.x; t < kWave * V; t += kThreads) {
+        const int64_t j = strip * kWave * V + t;
+        const int q = (t % V) * kWave + t / V;
+        if (j < a.N) part[p * a.br * a.N + r * a.N + j] = (sh[0][q] + sh[1][q]) + (sh[2][q] + sh[3][q]);
     }
 }
 
+// Columns' finish: a block takes 64 columns of one residue, its waves every
+// fourth partition.
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_vcol_finish(const T *C, VerifyArgs a, int64_t P, const double *part) {
-    const int64_t rel = a.br * a.N;
+__device__ inline void vcol_finish(const VerifyArgs &a, const T *C, int64_t blk, int64_t P, const double *part) {
+    __shared__ double sh[kThreads / kWave][kWave];
+    const int64_t cbs = (a.N + kWave - 1) / kWave, r = blk / cbs, j = (blk - r * cbs) * kWave + threadIdx.x % kWave;
+    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+    double s = 0.0;
+    if (j < a.N)
+        for (int64_t p = w; p < P; p += kThreads / kWave) s += part[p * a.br * a.N + r * a.N + j];
+    sh[w][lane] = s;
+    __syncthreads();
     double ratio = 0.0;
     unsigned long long excl = 0;
-    for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < rel; t += (int64_t)gridDim.x * kThreads) {
-        int64_t r = t / a.N, j = t - r * a.N;
-        double s = 0.0;
-        for (int64_t p = 0; p < P; ++p) s += part[p * rel + t];
-        finish_col<T>(a, C, r, j, s, ratio, excl);
-    }
+    if (w == 0 && j < a.N)
+        finish_col<T>(a, C, r, j, (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]), ratio, excl);
     fold_block(ratio, excl, &a.rep->max_ratio_c, &a.rep->n_excl_c);
 }
 
@@ -1124,11 +1160,11 @@ __device__ inline void finish_row(const VerifyArgs &a, const T *C, int64_t i, in
 
 // One thread per row relation; lanes take consecutive c (coalesced when bc >= 64).
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_vrow_strided(const T *C, VerifyArgs a) {
+__device__ inline void vrow_strided(const VerifyArgs &a, const T *C, int64_t blk, int64_t nblk) {
     const int64_t total = a.M * a.bc;
     double ratio = 0.0;
     unsigned long long excl = 0;
-    for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < total; t += (int64_t)gridDim.x * kThreads) {
+    for (int64_t t = blk * kThreads + threadIdx.x; t < total; t += nblk * kThreads) {
         int64_t i = t / a.bc, c = t - i * a.bc;
         const T *p = C + i * a.ldc + c;
         double s = 0.0;
@@ -1138,34 +1174,23 @@ __global__ __launch_bounds__(kThreads) void k_vrow_strided(const T *C, VerifyArg
     fold_block(ratio, excl, &a.rep->max_ratio_r, &a.rep->n_excl_r);
 }
 
-// One block per row for bc dividing 256: thread t sums the columns j = t mod 256,
-// all of residue t mod bc; a fixed-order tree then combines the 256/bc partial
-// sums of each residue.  With V > 1 (bc == 1 and 16-byte aligned rows) thread t
-// sums whole vectors t, t + 256, ... of the row.
-template <typename T, int V>
-__global__ __launch_bounds__(kThreads) void k_vrow_block(const T *C, VerifyArgs a) {
+// One block per row for bc < 64 dividing 256, any alignment: thread t sums the
+// columns j = t mod 256, all of residue t mod bc; a fixed-order tree then
+// combines the 256/bc partial sums of each residue.
+template <typename T>
+__device__ inline void vrow_block(const VerifyArgs &a, const T *C, int64_t blk, int64_t nblk) {
     __shared__ double sh[kThreads];
     double ratio = 0.0;
     unsigned long long excl = 0;
-    for (int64_t i = blockIdx.x; i < a.M; i += gridDim.x) {
+    for (int64_t i = blk; i < a.M; i += nblk) {
         const T *row = C + i * a.ldc;
-        double s0 = 0.0, s1 = 0.0, v[V], w[V];
-        int64_t j = (int64_t)threadIdx.x * V;
-        for (; j + kThreads * V < a.n; j += 2 * kThreads * V) {
-            load_c<T, V>(row + j, v);
-            load_c<T, V>(row + j + kThreads * V, w);
-#pragma unroll
-            for (int q = 0; q < V; ++q) {
-                if (j + q < a.n) s0 += v[q];
-                if (j + kThreads * V + q < a.n) s1 += w[q];
-            }
+        double s0 = 0.0, s1 = 0.0;
+        int64_t j = threadIdx.x;
+        for (; j + kThreads < a.n; j += 2 * kThreads) {
+            s0 += elem<T>::load(row + j);
+            s1 += elem<T>::load(row + j + kThreads);
         }
-        if (j < a.n) {
-            load_c<T, V>(row + j, v);
-#pragma unroll
-            for (int q = 0; q < V; ++q)
-                if (j + q < a.n) s0 += v[q];
-        }
+        if (j < a.n) s0 += elem<T>::load(row + j);
         sh[threadIdx.x] = s0 + s1;
         __syncthreads();
         for (int wd = kThreads / 2; wd >= a.bc; wd >>= 1) {
@@ -1176,6 +1201,70 @@ __global__ __launch_bounds__(kThreads) void k_vrow_block(const T *C, VerifyArgs 
         __syncthreads();
     }
     fold_block(ratio, excl, &a.rep->max_ratio_r, &a.rep->n_excl_r);
+}
+
+// The same with 16-byte loads (aligned rows): a wave per row, four loads in
+// flight.  A lane's V columns keep their residues from load to load (64 V is a
+// multiple of bc), so it holds V sums, folded at the end within the lane
+// (bc < V) and across the lanes that share them; lane l < max(1, bc / V) then
+// finishes residues l V + q.
+template <typename T, int V>
+__device__ inline void vrow_wave(const VerifyArgs &a, const T *C, int64_t blk, int64_t nblk) {
+    const int lane = threadIdx.x % kWave, bc = (int)a.bc;
+    double ratio = 0.0;
+    unsigned long long excl = 0;
+    for (int64_t i = blk * (kThreads / kWave) + threadIdx.x / kWave; i < a.M; i += nblk * (kThreads / kWave)) {
+        const T *row = C + i * a.ldc;
+        double s[V] = {}, v[4][V];
+        // a vector that starts before n stays inside its row; its elements at n and beyond are not summed
+        auto add = [&](const double (&x)[V], int64_t j) {
+#pragma unroll
+            for (int q = 0; q < V; ++q) s[q] += j + q < a.n ? x[q] : 0.0;
+        };
+        int64_t j = (int64_t)lane * V;
+        for (; j + 3 * kWave * V < a.n; j += 4 * kWave * V) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) load_c<T, V>(row + j + u * kWave * V, v[u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) add(v[u], j + u * kWave * V);
+        }
+        for (; j < a.n; j += kWave * V) {
+            load_c<T, V>(row + j, v[0]);
+            add(v[0], j);
+        }
+        for (int w = V / 2; w >= bc; w >>= 1) {
+#pragma unroll
+            for (int q = 0; q < V / 2; ++q)
+                if (q < w) s[q] += s[q + w < V ? q + w : q];
+        }
+        const int lanes = bc > V ? bc / V : 1;
+        for (int off = kWave / 2; off >= lanes; off >>= 1)
+#pragma unroll
+            for (int q = 0; q < V; ++q) s[q] += __shfl_xor(s[q], off);
+        if (lane < lanes) {
+#pragma unroll
+            for (int q = 0; q < V; ++q)
+                if (q < bc) finish_row<T>(a, C, i, lane * V + q, s[q], ratio, excl);
+        }
+    }
+    fold_block(ratio, excl, &a.rep->max_ratio_r, &a.rep->n_excl_r);
+}
+
+// Both directions' relations in one launch: blocks [0, nc) the columns (summed
+// here, or finished from P partitions' sums), the rest the rows.
+enum { ROWS_WAVE, ROWS_BLOCK, ROWS_STRIDED };
+template <typename T, int V>
+__global__ __launch_bounds__(kThreads) void k_vrelations(const T *C, VerifyArgs a, int64_t P, const double *part,
+                                                         unsigned nc, int rows) {
+    if (blockIdx.x < nc) {
+        if (part) vcol_finish<T>(a, C, blockIdx.x, P, part);
+        else vcol_direct<T, V>(a, C, blockIdx.x, nc);
+        return;
+    }
+    const int64_t blk = blockIdx.x - nc, nblk = gridDim.x - nc;
+    if (V > 1 && rows == ROWS_WAVE) vrow_wave<T, V>(a, C, blk, nblk);
+    else if (rows == ROWS_BLOCK) vrow_block<T>(a, C, blk, nblk);
+    else vrow_strided<T>(a, C, blk, nblk);
 }
 
 // Erasure tests of the one-pass kernel: the residues of each known
@@ -1357,151 +1446,162 @@ static void launch_vblock(const double *C, const VerifyArgs &a, const ErasureRes
 // epilogue writes for the fused verification; k_vfused then finishes the
 // relations.  A wave takes rows w, w + 4, ... of its tile, four at a time.
 constexpr int64_t kPartRows = kVerifyPartRows;
-template <typename T, int V>
+template <typename T, int V, bool NT>
 __global__ __launch_bounds__(kThreads) void k_vpartials(const T *C, int64_t ldc, int64_t m, int64_t n, double *pc,
-                                                        double *pr) {
+                                                        double *pr, abft_report *rep) {
     constexpr int NW = kThreads / kWave;
     constexpr int64_t TCW = (int64_t)kWave * V;
     __shared__ double sh[NW][TCW];
+    if (blockIdx.x == 0) clear_report(rep);            // nothing is recorded before the next launch
     const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
     const int64_t tiles_n = (n + TCW - 1) / TCW, tiles = ((m + kPartRows - 1) / kPartRows) * tiles_n;
     for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
         const int64_t tm = tile / tiles_n, tn = tile - tm * tiles_n;
         const int64_t i0 = tm * kPartRows, i1 = min(m, i0 + kPartRows), j0 = tn * TCW + lane * V;
-        double cs[V];
-#pragma unroll
-        for (int q = 0; q < V; ++q) cs[q] = 0.0;
+        double cs[V] = {};
         // rows of C are 16-byte aligned and ldc is a multiple of V: a vector that starts before n stays
         // inside its row; its elements at n and beyond are not summed
-        auto add_row = [&](const double (&v)[V], double &rs) {
+        const bool ok = j0 < n;
+        const T *src = C + (ok ? j0 : 0);
+        auto add_row = [&](const v4u32 &raw) {
+            double v[V], rs = 0.0;
+            vec16<T>::widen(raw, v);
 #pragma unroll
             for (int q = 0; q < V; ++q) {
                 const double x = j0 + q < n ? v[q] : 0.0;
                 cs[q] += x;
                 rs += x;
             }
+            return rs;
+        };
+        // four rows of the wave at a time, the next four requested before these are summed
+        auto request = [&](v4u32 (&raw)[4], int64_t i) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) raw[u] = load_raw<NT, v4u32>(src + (i + u * NW) * ldc);
         };
         int64_t i = i0 + w;
+        v4u32 next[4];
+        if (i + 3 * NW < i1) request(next, i);
         for (; i + 3 * NW < i1; i += 4 * NW) {
-            double v0[V], v1[V], v2[V], v3[V];
-            if (j0 < n) {
-                load_c<T, V>(C + i * ldc + j0, v0);
-                load_c<T, V>(C + (i + NW) * ldc + j0, v1);
-                load_c<T, V>(C + (i + 2 * NW) * ldc + j0, v2);
-                load_c<T, V>(C + (i + 3 * NW) * ldc + j0, v3);
-            } else {
+            v4u32 raw[4];
 #pragma unroll
-                for (int q = 0; q < V; ++q) v0[q] = v1[q] = v2[q] = v3[q] = 0.0;
-            }
-            double r0 = 0.0, r1 = 0.0, r2 = 0.0, r3 = 0.0;
-            add_row(v0, r0);
-            add_row(v1, r1);
-            add_row(v2, r2);
-            add_row(v3, r3);
-            r0 = wave_sum(r0);
-            r1 = wave_sum(r1);
-            r2 = wave_sum(r2);
-            r3 = wave_sum(r3);
-            if (lane == 0) {
-                pr[tn * m + i] = r0;
-                pr[tn * m + i + NW] = r1;
-                pr[tn * m + i + 2 * NW] = r2;
-                pr[tn * m + i + 3 * NW] = r3;
-            }
+            for (int u = 0; u < 4; ++u) raw[u] = next[u];
+            if (i + 7 * NW < i1) request(next, i + 4 * NW);
+            double q[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) q[u] = add_row(raw[u]);
+            // the four rows' sums by a reduce-scatter: 2 + 1 exchanges, then within 16 lanes
+            const bool hi = lane & 32, lo = lane & 16;
+            double k0 = hi ? q[2] : q[0], k1 = hi ? q[3] : q[1];
+            k0 += __shfl_xor(hi ? q[0] : q[2], 32);
+            k1 += __shfl_xor(hi ? q[1] : q[3], 32);
+            double x = lo ? k1 : k0;
+            x += __shfl_xor(lo ? k0 : k1, 16);
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) x += __shfl_xor(x, o);
+            if (lane % 16 == 0) pr[tn * m + i + (lane / 16) * NW] = x;
         }
         for (; i < i1; i += NW) {
-            double v0[V];
-            if (j0 < n) load_c<T, V>(C + i * ldc + j0, v0);
-            else {
-#pragma unroll
-                for (int q = 0; q < V; ++q) v0[q] = 0.0;
-            }
-            double r0 = 0.0;
-            add_row(v0, r0);
-            r0 = wave_sum(r0);
-            if (lane == 0) pr[tn * m + i] = r0;
+            const double x = wave_sum(add_row(load_raw<NT, v4u32>(src + i * ldc)));
+            if (lane == 0) pr[tn * m + i] = x;
         }
 #pragma unroll
-        for (int q = 0; q < V; ++q) sh[w][lane * V + q] = cs[q];
+        for (int q = 0; q < V; ++q) sh[w][q * kWave + lane] = cs[q];
         __syncthreads();
         for (int64_t c = threadIdx.x; c < TCW; c += kThreads) {
-            const int64_t j = tn * TCW + c;
-            double t = 0.0;
-#pragma unroll
-            for (int q = 0; q < NW; ++q) t += sh[q][c];
-            if (j < n) pc[tm * n + j] = t;
+            const int64_t j = tn * TCW + c, q = (c % V) * kWave + c / V;
+            if (j < n) pc[tm * n + j] = (sh[0][q] + sh[1][q]) + (sh[2][q] + sh[3][q]);
         }
         __syncthreads();
     }
 }
 
-// Fused verification (b = 1): the column relations of the data columns and
-// the row relations of the data rows from the product epilogue's partial
-// sums (pc: tiles_m x n, pr: tiles_n x m, summed over the tiles in a fixed
-// order: four running sums over tiles q mod 4, then pairwise);
-// the carried column and the carried row are summed from C_f directly.
+// Verification from partial sums (b = 1): the column relations of the data
+// columns and the row relations of the data rows from tile sums (pc: tiles_m x
+// n, pr: tiles_n x m), added in a fixed order -- a block takes 64 relations, its
+// four waves every fourth tile; the first two blocks, the longest, sum the carried
+// column C_f[0:m, n] and the carried row C_f[m, 0:n] against the corner.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_vfused(const T *C, VerifyArgs a, const double *pc, const double *pr,
                                                      int64_t tiles_m, int64_t tiles_n) {
     if (a.tag && *a.tag != a.key) return;     // partials of another product: nothing is recorded
-    double rc = 0.0, rr = 0.0;
-    unsigned long long ec = 0, er = 0;
-    const int64_t total = a.n + a.m;
-    for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < total; t += (int64_t)gridDim.x * kThreads) {
-        // four independent running sums (tiles q mod 4) keep four loads in flight
-        auto sum4 = [](const double *x, int64_t stride, int64_t cnt) {
-            double s4[4] = {0.0, 0.0, 0.0, 0.0};
-            int64_t q = 0;
-            for (; q + 3 < cnt; q += 4) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) s4[e] += x[(q + e) * stride];
-            }
-            for (int e = 0; q < cnt; ++q, ++e) s4[e] += x[q * stride];
-            return (s4[0] + s4[1]) + (s4[2] + s4[3]);
-        };
-        if (t < a.n) {
-            finish_col<T>(a, C, 0, t, sum4(pc + t, a.n, tiles_m), rc, ec);
-        } else {
-            const int64_t i = t - a.n;
-            finish_row<T>(a, C, i, 0, sum4(pr + i, a.m, tiles_n), rr, er);
-        }
-    }
-    fold_block(rc, ec, &a.rep->max_ratio_c, &a.rep->n_excl_c);
-    __syncthreads();   // fold_block's shared slots are reused by the second fold
-    fold_block(rr, er, &a.rep->max_ratio_r, &a.rep->n_excl_r);
-}
-
-// Block 0: the carried column C_f[0:m, n] against the corner; block 1: the
-// carried row C_f[m, 0:n] against the corner.  Fixed-order block reductions.
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_vfused_edges(const T *C, VerifyArgs a) {
-    if (a.tag && *a.tag != a.key) return;
+    constexpr int NW = kThreads / kWave;
     __shared__ double sh[kThreads];
-    const bool col = blockIdx.x == 0;
-    const int64_t len = col ? a.m : a.n;
-    // element t of the carried column (row); four running sums keep four loads in flight (the tail goes to the first)
-    auto at = [&](int64_t t) { return col ? elem<T>::load(C + t * a.ldc + a.n) : elem<T>::load(C + a.m * a.ldc + t); };
-    double s4[4] = {0.0, 0.0, 0.0, 0.0};
-    int64_t t = threadIdx.x;
-    for (; t + 3 * kThreads < len; t += 4 * kThreads) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s4[e] += at(t + e * kThreads);
-    }
-    for (; t < len; t += kThreads) s4[0] += at(t);
-    sh[threadIdx.x] = (s4[0] + s4[1]) + (s4[2] + s4[3]);
-    __syncthreads();
-    for (int w = kThreads / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
+    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+    const int64_t nbc = (a.n + kWave - 1) / kWave, blk = (int64_t)blockIdx.x - 2;
     double ratio = 0.0;
     unsigned long long excl = 0;
-    if (threadIdx.x == 0) {
-        if (col) finish_col<T>(a, C, 0, a.n, sh[0], ratio, excl);
-        else finish_row<T>(a, C, a.m, 0, sh[0], ratio, excl);
+    bool col;
+    if (blk >= 0) {
+        col = blk < nbc;
+        const int64_t len = col ? a.n : a.m, t = (col ? blk : blk - nbc) * kWave + lane;
+        const int64_t tiles = col ? tiles_m : tiles_n;
+        const double *x = (col ? pc : pr) + t;
+        double s4[4] = {};
+        if (t < len) {
+            int64_t q = w;
+            for (; q + 3 * NW < tiles; q += 4 * NW) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s4[e] += x[(q + e * NW) * len];
+            }
+            for (int e = 0; q < tiles; q += NW, ++e) s4[e] += x[q * len];
+        }
+        sh[threadIdx.x] = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+        __syncthreads();
+        if (w == 0 && t < len) {
+            const double s = (sh[lane] + sh[kWave + lane]) + (sh[2 * kWave + lane] + sh[3 * kWave + lane]);
+            if (col) finish_col<T>(a, C, 0, t, s, ratio, excl);
+            else finish_row<T>(a, C, t, 0, s, ratio, excl);
+        }
+    } else {
+        col = blk == -2;
+        const int64_t len = col ? a.m : a.n;
+        // element t of the carried column (row); sixteen loads in flight (the column's are a line each)
+        auto at = [&](int64_t t) { return col ? elem<T>::load(C + t * a.ldc + a.n) : elem<T>::load(C + a.m * a.ldc + t); };
+        double s8[8] = {};
+        int64_t t = threadIdx.x;
+        for (; t + 15 * kThreads < len; t += 16 * kThreads) {
+            double x[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) x[e] = at(t + e * kThreads);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) s8[e % 8] += x[e];
+        }
+        for (; t + 3 * kThreads < len; t += 4 * kThreads) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s8[e] += at(t + e * kThreads);
+        }
+        for (; t < len; t += kThreads) s8[0] += at(t);
+        sh[threadIdx.x] = ((s8[0] + s8[1]) + (s8[2] + s8[3])) + ((s8[4] + s8[5]) + (s8[6] + s8[7]));
+        __syncthreads();
+        for (int h = kThreads / 2; h > 0; h >>= 1) {
+            if (threadIdx.x < h) sh[threadIdx.x] += sh[threadIdx.x + h];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) {
+            if (col) finish_col<T>(a, C, 0, a.n, sh[0], ratio, excl);
+            else finish_row<T>(a, C, a.m, 0, sh[0], ratio, excl);
+        }
     }
     if (col) fold_block(ratio, excl, &a.rep->max_ratio_c, &a.rep->n_excl_c);
     else fold_block(ratio, excl, &a.rep->max_ratio_r, &a.rep->n_excl_r);
+}
+template <typename T>
+static void launch_vfused(const T *C, const VerifyArgs &a, const double *pc, const double *pr, int64_t tiles_m,
+                          int64_t tiles_n, hipStream_t s) {
+    const unsigned blocks = (unsigned)((a.n + kWave - 1) / kWave + (a.m + kWave - 1) / kWave + 2);
+    k_vfused<T><<<blocks, kThreads, 0, s>>>(C, a, pc, pr, tiles_m, tiles_n);
+}
+
+// Whether a problem's relations are verified by k_vblock (wide checksum blocks,
+// few of them per row: both directions from one read of C).  Its threads walk
+// the block rows two at a time, so with fewer threads it pays while there are few
+// block rows: 2304 x 2304 binary64 with 256-blocks 72 us by columns and by rows,
+// 21 here; 320 x 320 with 64-blocks 10 in one launch of both, 12 here.
+static bool block_pass(const Geom &g, bool f64, bool vec) {
+    const int64_t threads = g.br * (g.bc / 2);
+    return f64 && vec && g.bc % 2 == 0 && g.bc >= 64 && g.Gc <= kBlockPassMaxG &&
+           (threads >= 65536 || (threads >= 16384 && g.Gr <= 16));
 }
 
 template <typename T>
@@ -1522,15 +1622,13 @@ static int verify_typed(const abft_problem *p, const T *C, const Erasures &er, c
     a.scale_exp = p->dtype == ABFT_FP8_E4M3 ? (const int *)(ws + L.scale) : nullptr;
     a.rep = sc.rep;
     a.er = er;
-    k_report_init<<<1, kThreads, 0, s>>>(a.rep);
     auto blocks = [](int64_t work) { return (unsigned)std::min<int64_t>((work + kThreads - 1) / kThreads, 4096); };
     // 16-byte loads when every row of C starts on a 16-byte boundary
     constexpr int VV = 16 / (int)sizeof(T);
     const bool vec = ((uintptr_t)C % 16 == 0) && (p->ldc % VV == 0);
-    const int64_t V = vec ? VV : 1;
     // wide checksum blocks with few groups per row: one pass for both directions
-    if (sizeof(T) == 8 && vec && g.bc % VV == 0 && g.bc >= 64 && g.Gc <= kBlockPassMaxG &&
-        g.br * (g.bc / VV) >= 65536) {
+    if (block_pass(g, sizeof(T) == 8, vec)) {
+        k_report_init<<<1, kThreads, 0, s>>>(a.rep);
         const double *Cd = (const double *)C;
         const ErasureRes ex = erasure_res(er, g.br, g.bc);
         const unsigned grid = blocks(g.br * (g.bc / 2));
@@ -1551,31 +1649,32 @@ static int verify_typed(const abft_problem *p, const T *C, const Erasures &er, c
     if (g.br == 1 && g.bc == 1 && vec) {
         double *pc = sc.vpart_c, *pr = sc.vpart_r;
         const int64_t tiles_m = (g.m + kPartRows - 1) / kPartRows, tiles_n = (g.n + kWave * VV - 1) / (kWave * VV);
-        k_vpartials<T, VV><<<(unsigned)std::min<int64_t>(tiles_m * tiles_n, 8192), kThreads, 0, s>>>(C, p->ldc, g.m,
-                                                                                                   g.n, pc, pr);
-        k_vfused<T><<<blocks(g.n + g.m), kThreads, 0, s>>>(C, a, pc, pr, tiles_m, tiles_n);
-        k_vfused_edges<T><<<2, kThreads, 0, s>>>(C, a);
+        const unsigned grid = (unsigned)std::min<int64_t>(tiles_m * tiles_n, 8192);
+        if (streams(g.m * g.n * (int64_t)sizeof(T)))
+            k_vpartials<T, VV, true><<<grid, kThreads, 0, s>>>(C, p->ldc, g.m, g.n, pc, pr, a.rep);
+        else
+            k_vpartials<T, VV, false><<<grid, kThreads, 0, s>>>(C, p->ldc, g.m, g.n, pc, pr, a.rep);
+        launch_vfused<T>(C, a, pc, pr, tiles_m, tiles_n, s);
         ABFT_LAUNCHED();
         return ABFT_OK;
     }
-    int64_t P = group_partitions(g.Gr, g.br, (g.N + V - 1) / V);
-    if (P == 1) {
-        if (vec) k_vcol_direct<T, VV><<<blocks(g.br * ((g.N + VV - 1) / VV)), kThreads, 0, s>>>(C, a);
-        else k_vcol_direct<T, 1><<<blocks(g.br * g.N), kThreads, 0, s>>>(C, a);
+    const VcolSplit sp = vcol_split(g, vec ? VV : 1);
+    unsigned nc;
+    if (sp.direct) {
+        k_report_init<<<1, kThreads, 0, s>>>(a.rep);
+        nc = blocks(g.br * (vec ? (g.N + VV - 1) / VV : g.N));
     } else {
-        int64_t chunk = (g.Gr + P - 1) / P;
-        P = (g.Gr + chunk - 1) / chunk;
-        double *part = sc.partial;
-        if (vec) k_vcol_partial<T, VV><<<blocks(P * g.br * ((g.N + VV - 1) / VV)), kThreads, 0, s>>>(C, a, P, chunk, part);
-        else k_vcol_partial<T, 1><<<blocks(P * g.br * g.N), kThreads, 0, s>>>(C, a, P, chunk, part);
-        k_vcol_finish<T><<<blocks(g.br * g.N), kThreads, 0, s>>>(C, a, P, part);
+        const unsigned grid = (unsigned)(sp.strips * g.br * sp.P);
+        if (vec) k_vcol_partial<T, VV><<<grid, kThreads, 0, s>>>(C, a, sp, sc.partial);
+        else k_vcol_partial<T, 1><<<grid, kThreads, 0, s>>>(C, a, sp, sc.partial);
+        nc = (unsigned)(g.br * ((g.N + kWave - 1) / kWave));
     }
-    if (g.bc == 1 && vec)
-        k_vrow_block<T, VV><<<(unsigned)std::min<int64_t>(g.M, 8192), kThreads, 0, s>>>(C, a);
-    else if (g.bc < 64 && (kThreads % g.bc) == 0)
-        k_vrow_block<T, 1><<<(unsigned)std::min<int64_t>(g.M, 8192), kThreads, 0, s>>>(C, a);
-    else
-        k_vrow_strided<T><<<blocks(g.M * g.bc), kThreads, 0, s>>>(C, a);
+    const int rows = g.bc < 64 && kThreads % g.bc == 0 ? (vec ? ROWS_WAVE : ROWS_BLOCK) : ROWS_STRIDED;
+    const unsigned nr = rows == ROWS_STRIDED ? blocks(g.M * g.bc)
+                        : (unsigned)std::min<int64_t>(rows == ROWS_WAVE ? (g.M + 3) / 4 : g.M, 4096);
+    const double *part = sp.direct ? nullptr : sc.partial;
+    if (vec) k_vrelations<T, VV><<<nc + nr, kThreads, 0, s>>>(C, a, sp.P, part, nc, rows);
+    else k_vrelations<T, 1><<<nc + nr, kThreads, 0, s>>>(C, a, sp.P, part, nc, rows);
     ABFT_LAUNCHED();
     return ABFT_OK;
 }
@@ -1601,10 +1700,7 @@ static int verify_fused_typed(const abft_problem *p, const T *C, char *ws, int64
     a.tag = (const uint64_t *)(ws + L.fused_tag);
     a.key = key;
     k_report_init_tag<<<1, kThreads, 0, s>>>(a.rep, a.tag, key);
-    const unsigned blocks = (unsigned)std::min<int64_t>((g.n + g.m + kThreads - 1) / kThreads, 4096);
-    k_vfused<T><<<blocks, kThreads, 0, s>>>(C, a, (const double *)(ws + L.fused_c), (const double *)(ws + L.fused_r),
-                                            tiles_m, tiles_n);
-    k_vfused_edges<T><<<2, kThreads, 0, s>>>(C, a);
+    launch_vfused<T>(C, a, (const double *)(ws + L.fused_c), (const double *)(ws + L.fused_r), tiles_m, tiles_n, s);
     ABFT_LAUNCHED();
     return ABFT_OK;
 }
@@ -1633,24 +1729,21 @@ size_t verify_scratch_layout(const abft_problem *p, const void *C_f, char *base,
     const bool f64 = p->dtype == ABFT_F64;
     const int64_t VV = f64 ? 2 : 4;
     const bool vec = ((uintptr_t)C_f % 16 == 0) && (p->ldc % VV == 0);
-    const int64_t V = vec ? VV : 1;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = (off + bytes + 255) & ~(size_t)255; return o; };
     const size_t rep = take(sizeof(abft_report));
     size_t pc = 0, pr = 0, part = 0;
     bool use_pc = false, use_part = false;
-    const bool block_pass = f64 && vec && g.bc % VV == 0 && g.bc >= 64 && g.Gc <= kBlockPassMaxG &&
-                            g.br * (g.bc / VV) >= 65536;
-    if (!block_pass) {
+    if (!block_pass(g, f64, vec)) {
         if (g.br == 1 && g.bc == 1 && vec) {
             const int64_t tiles_m = (g.m + kPartRows - 1) / kPartRows, tiles_n = (g.n + kWave * VV - 1) / (kWave * VV);
             pc = take(sizeof(double) * tiles_m * g.n);
             pr = take(sizeof(double) * tiles_n * g.m);
             use_pc = true;
         } else {
-            const int64_t P = group_partitions(g.Gr, g.br, (g.N + V - 1) / V);
-            if (P > 1) {
-                part = take(sizeof(double) * P * g.br * g.N);
+            const VcolSplit sp = vcol_split(g, vec ? (int)VV : 1);
+            if (!sp.direct) {
+                part = take(sizeof(double) * sp.P * g.br * g.N);
                 use_part = true;
             }
         }
