@@ -18,7 +18,7 @@
 //
 // Rows beyond M (columns beyond N) load a clamped valid row; they only feed
 // results that are not stored.  K must be a multiple of the slab (128 bytes);
-// other K use the padded-LDS kernel of gemm_lowp_kernel.h.
+// other K use the half-slab ring of gemm_lowp_ring_kernel.h.
 #pragma once
 
 #include "gemm_lowp_kernel.h"
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(128 * WM, 1) void k_gemm_lowp2(const typename Ops::
     tile_of<GROUP_M>(blockIdx.x, gridDim.x, tiles_m, tiles_n, tm, tn);
     const int64_t row0 = tm * BM, col0 = tn * BN;
 
-    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     const int wm = wave / 2, wn = wave % 2;
     constexpr int NW = 2 * WM;                         // waves per block
     constexpr int LPW = 32 / NW;                       // load instructions per wave and operand

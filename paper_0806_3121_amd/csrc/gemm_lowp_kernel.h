@@ -1,5 +1,6 @@
 // Low-precision products with binary32 accumulation on the gfx950 matrix
-// cores, templated on the element type and the tile shape:
+// cores, templated on the element type and the tile shape (the tile function
+// of the batched product, and the instruction wrappers of every kernel):
 //   bfloat16: v_mfma_f32_16x16x32_bf16 (16 x 16 x 32 per instruction)
 //   FP8 E4M3 (OCP e4m3fn): v_mfma_f32_16x16x32_fp8_fp8
 // A is row-major and B column-major (Bt row-major), both k-contiguous.  Each
@@ -197,38 +198,6 @@ __device__ inline void lowp_tile(const typename T::E *__restrict__ A, int64_t ld
             }
         }
     }
-}
-
-template <class T, bool FUSED>
-__global__ __launch_bounds__(T::THREADS, T::MINB) void k_gemm_lowp(const typename T::E *__restrict__ A, int64_t lda,
-                                                             const typename T::E *__restrict__ Bt, int64_t ldb,
-                                                             float *__restrict__ C, int64_t ldc, int64_t M, int64_t N,
-                                                             int64_t K, const int *__restrict__ scale_exp,
-                                                             EpiArgs epi) {
-    __shared__ __attribute__((aligned(16))) typename T::E lds[2 * T::BUF];
-    const int64_t tiles_m = (M + T::BM - 1) / T::BM, tiles_n = (N + T::BN - 1) / T::BN;
-    int64_t tm, tn;
-    tile_of<T::GROUP_M>(blockIdx.x, gridDim.x, tiles_m, tiles_n, tm, tn);
-    const int sh = scale_exp ? -(scale_exp[0] + scale_exp[1]) : 0;      // scale back by 2^sh with ldexp
-    lowp_tile<T, FUSED>(A, lda, Bt, ldb, C, ldc, M, N, K, sh, tm * T::BM, tn * T::BN, lds, epi, tm, tn);
-}
-
-template <class T>
-inline int launch_gemm_lowp_tile(const typename T::E *A, int64_t lda, const typename T::E *Bt, int64_t ldb, float *C,
-                                 int64_t ldc, int64_t M, int64_t N, int64_t K, const int *scale_exp, hipStream_t s,
-                                 EpiArgs *epi = nullptr) {
-    int64_t tiles = ((M + T::BM - 1) / T::BM) * ((N + T::BN - 1) / T::BN);
-    if (tiles > INT32_MAX) return ABFT_E_ARG;
-    EpiArgs e = epi ? *epi : epi_none();
-    if (epi) {
-        epi->tiles_m = (M + T::BM - 1) / T::BM;
-        epi->tiles_n = (N + T::BN - 1) / T::BN;
-    }
-    if (e.pc)
-        k_gemm_lowp<T, true><<<(unsigned)tiles, T::THREADS, 0, s>>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, e);
-    else
-        k_gemm_lowp<T, false><<<(unsigned)tiles, T::THREADS, 0, s>>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, e);
-    return ABFT_OK;
 }
 
 }  // namespace abft

@@ -2,7 +2,7 @@
 //
 // The data part and any thick checksum block (b > kSliverMaxB) run on the
 // matrix cores (gemm_mfma2_kernel.h / gemm_mfma_kernel.h for binary64 and
-// binary32, gemm_lowp2_kernel.h / gemm_lowp_kernel.h for bfloat16 and FP8).
+// binary32, gemm_lowp2_kernel.h / gemm_lowp_ring_kernel.h for bfloat16 and FP8).
 // A thin checksum block (b <= kSliverMaxB, e.g. the classic b = 1) would
 // occupy a whole row or column of tiles for a few useful rows, so it is
 // computed instead by the skinny-product kernel (sliver_kernel.h), which
@@ -10,7 +10,7 @@
 // lives in one function per element type, used by the launch and by
 // abft_describe_gemm alike.
 #include "gemm_lowp2_kernel.h"
-#include "gemm_lowp_kernel.h"
+#include "gemm_lowp_ring_kernel.h"
 #include "gemm_mfma2_kernel.h"
 #include "gemm_mfma_kernel.h"
 #include "sliver_kernel.h"
@@ -88,7 +88,7 @@ static const TileChoice kF32Tiles[] = {
 
 // The data-part kernel and tile for an M x N x K product of element type E.
 struct MainPick {
-    bool direct;            // direct-to-LDS kernel (else register-staged / padded-LDS)
+    bool direct;            // direct-to-LDS kernel with one barrier per slab (else register-staged / half-slab ring)
     const TileChoice *t;
 };
 // Whether an M x N x K product (K in slabs of BK) is picked from the direct
@@ -213,31 +213,42 @@ static int protected_product(const abft_problem *p, const Geom &g, const E *A, c
     return ABFT_OK;
 }
 
-// bfloat16 / FP8 candidates.  When k is a multiple of the 128-byte slab the
-// direct-to-LDS kernel runs (measured at 16384^3: bfloat16 53%, FP8 through
-// the 32x32x64 instruction 49%); otherwise the padded-LDS kernel, on a 256 x 256
-// or 128 x 128 tile (bfloat16 41% / 30% at 16384^3).
+// bfloat16 / FP8 candidates, picked by rounds.  eff orders the tiles as measured
+// (us, 256x256 / 256x128 / 128x128 / 64x64): bfloat16 4096^3 106 / 132 / 149 / 246,
+// 3000 x 5003 x 2056 70 / 95 / 106 / 211, 2048^3 43 / 31 / 24 / 34, 440 x 11551 x 1832
+// 58 / 45 / 55 / 71, 1487 x 2294 x 1824 46 / 34 / 24 / 34, 861 x 765 x 4504
+// 124 / 93 / 64 / 27, 1024^3 23 / 15 / 11 / 8.0; FP8 3000 x 5003 x 2064
+// 47 / 60 / 63 / 113, 1570 x 3468 x 880 27 / 20 / 20 / 22, 2048^3 29 / 22 / 17 / 21,
+// 861 x 765 x 4512 50 / 44 / 34 / 16.  The 64 x 64 tile is not offered to a fused
+// epilogue, whose sums have no room for it, nor below eight slabs of k, where a
+// launch is mostly its start and stores (FP8 500 x 600 x 528: 10.9 us with either
+// small tile).
+// When k is a multiple of the 128-byte slab the 256 x 256 tile runs in the kernel
+// with one barrier per slab (4096^3: 98 us against the ring's 106, 16384^3 6.4 ms
+// against 7.2); a masked last slab costs that one more registers than it has.
 static const TileChoice kLowpTiles[] = {
-    {0, 256, 256, 1, 0.411}, {1, 128, 128, 2, 0.303},
+    {0, 256, 256, 1, 0.50}, {3, 256, 128, 1, 0.35}, {1, 128, 128, 2, 0.31}, {2, 64, 64, 4, 0.19},
 };
-static const TileChoice kLowpDirectTile = {0, 256, 256, 1, 0.49};
-static MainPick pick_main_lowp(int64_t elem_size, int64_t M, int64_t N, int64_t K) {
-    if (K % (128 / elem_size) == 0 && M * N >= (int64_t)256 * 256 * 256) return {true, &kLowpDirectTile};
-    return {false, &kLowpTiles[choose_tile(kLowpTiles, 2, M, N)]};
+static MainPick pick_main_lowp(int64_t elem_size, int64_t M, int64_t N, int64_t K, bool fused) {
+    const int64_t slab = 128 / elem_size;
+    const TileChoice *t = &kLowpTiles[choose_rounds(kLowpTiles, fused || K < 8 * slab ? 3 : 4, M, N)];
+    return {t->bm == 256 && t->bn == 256 && K % slab == 0, t};
 }
-template <class Ops, class Ops2>
+template <class Ops>
 static int gemm_main_lowp(const typename Ops::E *A, int64_t lda, const typename Ops::E *Bt, int64_t ldb, float *C,
                           int64_t ldc, int64_t M, int64_t N, int64_t K, const int *scale_exp, hipStream_t s,
                           EpiArgs *e = nullptr) {
-    const MainPick pk = pick_main_lowp((int64_t)sizeof(typename Ops::E), M, N, K);
-    if (pk.direct) return launch_gemm_lowp2<Ops2, 4>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
+    const MainPick pk = pick_main_lowp((int64_t)sizeof(typename Ops::E), M, N, K, e && e->pc);
+    if (pk.direct) return launch_gemm_lowp2<Ops, 4>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
     switch (pk.t->id) {
     case 0:
-        return launch_gemm_lowp_tile<LowpTile<Ops, 256, 256, 128 / sizeof(typename Ops::E), 4, 2>>(
-            A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
+        return launch_gemm_lowp<LowpRing<Ops, 256, 256, 4, 2, 1>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
+    case 2:
+        return launch_gemm_lowp<LowpRing<Ops, 64, 64, 2, 2, 4>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
+    case 3:
+        return launch_gemm_lowp<LowpRing<Ops, 256, 128, 4, 2, 1>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
     default:
-        return launch_gemm_lowp_tile<LowpTile<Ops, 128, 128, 64, 2, 2, 8, 2>>(A, lda, Bt, ldb, C, ldc, M, N, K,
-                                                                              scale_exp, s, e);
+        return launch_gemm_lowp<LowpRing<Ops, 128, 128, 2, 2, 2>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
     }
 }
 
@@ -245,13 +256,13 @@ static int gemm_main_lowp(const typename Ops::E *A, int64_t lda, const typename 
 // block from the binary32 checksum rows in the workspace (Acs: br x k,
 // Bcs: bc x k) with binary64 accumulation; FP8 results are scaled back by
 // 2^-(eA + eB) on the device.
-template <class Ops, class Ops2>
+template <class Ops>
 static int protected_product_lowp(const abft_problem *p, const Geom &g, const typename Ops::E *A,
                                   const typename Ops::E *Bt, float *C, const float *Acs, const float *Bcs,
                                   const int *scale_exp, bool plain, hipStream_t s, EpiArgs *e = nullptr,
                                   TagStore *tag = nullptr) {
     typedef typename Ops::E E;
-    int st = gemm_main_lowp<Ops, Ops2>(A, p->lda, Bt, p->ldb, C, p->ldc, g.m, g.n, g.k, scale_exp, s, e);
+    int st = gemm_main_lowp<Ops>(A, p->lda, Bt, p->ldb, C, p->ldc, g.m, g.n, g.k, scale_exp, s, e);
     if (st) return st;
     ABFT_LAUNCHED();
     if (plain) return ABFT_OK;
@@ -325,7 +336,7 @@ int describe_gemm(const abft_problem *p, uint32_t flags, char *buf, size_t len) 
         thin_r = thin_c = !plain;             // every carried block from the workspace checksum rows
         Mm = g.m;
         Nm = g.n;
-        pk = pick_main_lowp(p->dtype == ABFT_BF16 ? 2 : 1, Mm, Nm, g.k);
+        pk = pick_main_lowp(p->dtype == ABFT_BF16 ? 2 : 1, Mm, Nm, g.k, flags & ABFT_FUSED);
         kname = pk.direct ? "k_gemm_lowp2" : "k_gemm_lowp";
     } else {
         thin_r = !plain && g.S * g.br <= kSliverMaxB;
@@ -359,7 +370,7 @@ uint64_t fused_key(const abft_problem *p, const void *C_f, int64_t *tiles_m, int
     const Geom g = geom_of(p);
     const bool lowp = p->dtype == ABFT_BF16 || p->dtype == ABFT_FP8_E4M3;
     // b = 1: the carried row and column are slivers, the main product covers m x n
-    const MainPick pk = lowp ? pick_main_lowp(p->dtype == ABFT_BF16 ? 2 : 1, g.m, g.n, g.k)
+    const MainPick pk = lowp ? pick_main_lowp(p->dtype == ABFT_BF16 ? 2 : 1, g.m, g.n, g.k, true)
                              : (p->dtype == ABFT_F64 ? pick_main((const double *)nullptr, g.m, g.n, g.k, true)
                                                      : pick_main((const float *)nullptr, g.m, g.n, g.k, true));
     *tiles_m = (g.m + pk.t->bm - 1) / pk.t->bm;
@@ -385,11 +396,11 @@ static int product_with_extras(const abft_problem *p, const Geom &g, const void 
         return protected_product<float>(p, g, (const float *)A_f, (const float *)B_f, (float *)C_f, plain, s, 0, -1,
                                         false, e, tag);
     case ABFT_BF16:
-        return protected_product_lowp<Bf16Ops, Bf16Ops>(p, g, (const uint16_t *)A_f, (const uint16_t *)B_f,
-                                                        (float *)C_f, Acs, Bcs, nullptr, plain, s, e, tag);
+        return protected_product_lowp<Bf16Ops>(p, g, (const uint16_t *)A_f, (const uint16_t *)B_f, (float *)C_f,
+                                               Acs, Bcs, nullptr, plain, s, e, tag);
     case ABFT_FP8_E4M3:
-        return protected_product_lowp<Fp8Ops, Fp8x64Ops>(p, g, (const uint8_t *)A_f, (const uint8_t *)B_f,
-                                                         (float *)C_f, Acs, Bcs, scale, plain, s, e, tag);
+        return protected_product_lowp<Fp8x64Ops>(p, g, (const uint8_t *)A_f, (const uint8_t *)B_f, (float *)C_f,
+                                                 Acs, Bcs, scale, plain, s, e, tag);
     default:
         return ABFT_E_UNSUPPORTED;
     }
