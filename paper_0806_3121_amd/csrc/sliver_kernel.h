@@ -210,13 +210,19 @@ __global__ __launch_bounds__(kSliverThreads) void k_sliver(SliverJob<TX, TY, TC>
     sliver_launch<TX, TY, TC, 1, NY, UK, NT>(a, b, x);
 }
 // Few checksum rows over enough operand rows to fill the device: a wave takes
-// four operand rows, so each chunk of Y is read once for the four.  Per row the
-// same sums in the same order as k_sliver.
-constexpr int kSliverRows = 4;
+// several operand rows, so each chunk of Y is read once for them.  Per row the
+// same sums in the same order as k_sliver.  HBM-bound: what counts is the bytes
+// in flight and how often Y is read.  binary64, whose chunk is only two k, takes
+// two rows and four chunks (17408 x 16384, two checksum rows: 368 us, 6.2 TB/s;
+// four rows and one chunk 409, two and two 383, one and eight 444); the shorter
+// types four rows and one chunk (two rows: binary32 16384 x 16384 169 us against
+// 163, FP8 16384 x 16384 twice 138 against 120, bfloat16 16384 x 1024 twice 25
+// against 22).
+template <typename TX> constexpr int kSliverRows = sizeof(TX) == 8 ? 2 : 4;
 template <typename TX, typename TY, typename TC, int NY, bool NT>
 __global__ __launch_bounds__(kSliverThreads) void k_sliver1(SliverJob<TX, TY, TC> a, SliverJob<TX, TY, TC> b,
                                                            SliverExtra x) {
-    sliver_launch<TX, TY, TC, kSliverRows, NY, 1, NT>(a, b, x);
+    sliver_launch<TX, TY, TC, kSliverRows<TX>, NY, sizeof(TX) == 8 ? 4 : 1, NT>(a, b, x);
 }
 inline bool sliver_multirow(int64_t R, int64_t U) { return R <= 2 && U >= 16384; }
 
@@ -231,7 +237,7 @@ inline int slivers(SliverJob<TX, TY, TC> a, const SliverJob<TX, TY, TC> *b, cons
         const int64_t per_block = kSliverThreads / 64;
         const bool multi = sliver_multirow(u.R, u.U);
         auto blocks = [&](const Job &j) {
-            const int64_t waves = multi ? (j.U + kSliverRows - 1) / kSliverRows : j.U;
+            const int64_t waves = multi ? (j.U + kSliverRows<TX> - 1) / kSliverRows<TX> : j.U;
             return (unsigned)std::min<int64_t>((waves + per_block - 1) / per_block, 4096);
         };
         u.blocks = blocks(u);
