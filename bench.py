@@ -74,10 +74,10 @@ FLIP_BITS = {"f64": (40, 62), "f32": (24, 29), "bf16": (24, 29), "fp8": (24, 29)
 # summarized in profiles/hbm_traffic_counters_c2_c2b1_c2panel_c2w_c4_c5.txt.  Re-measure when those kernels change.
 TRAFFIC = {
     "c2": 41.728e9 + 0.679e9,                       # k_gemm_mfma2 (checksum blocks tiled with the data)
-    "c2b1": 40.120e9 + 0.562e9 + 2 * 0.538e9,       # k_gemm_mfma2 + two k_sliver launches
+    "c2b1": 40.120e9 + 0.562e9 + 2 * 0.538e9,       # k_gemm_mfma2 + the carried row and column
     "c2panel": 3.832e9 + 0.679e9,                   # one accumulating panel launch of k_gemm_mfma2
     "c2w": 41.595e9 + 0.680e9,                      # k_gemm_mfma2 over the weighted-checksum C_f
-    "c4": 14.040e9 + 1.120e9 + 2 * 0.538e9,         # k_gemm_lowp2 + two k_sliver1 launches
+    "c4": 14.040e9 + 1.120e9 + 2 * 0.538e9,         # k_gemm_lowp2 + the carried row and column
     "c5": 4.361e9 + 2.650e9 + 0.225e9 + 0.087e9,    # kb_gemm (the chosen 256 x 256 launch) + kb_combine
 }
 SEED = 20080523
