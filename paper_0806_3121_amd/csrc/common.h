@@ -94,6 +94,9 @@ template <> struct elem<uint8_t> {    // FP8 E4M3 storage (values in the scaled 
 };
 
 // One 16-byte load of N elements, widened to binary64 (16-byte aligned address).
+// widen: the same N values from a chunk already loaded as raw words; widen_part:
+// its elements P p .. P p + P - 1, so that a loop over the parts of several
+// chunks holds few of the widened values at a time.
 typedef uint32_t v4u32 __attribute__((ext_vector_type(4)));
 template <typename T> struct vec16;
 template <> struct vec16<double> {
@@ -103,11 +106,12 @@ template <> struct vec16<double> {
         v2 v = *(const v2 *)p;
         o[0] = v[0]; o[1] = v[1];
     }
-    // the same N values from a chunk already loaded as raw words
     __device__ static void widen(const v4u32 &w, double *o) {
         o[0] = __hiloint2double((int)w[1], (int)w[0]);
         o[1] = __hiloint2double((int)w[3], (int)w[2]);
     }
+    static constexpr int P = 2;
+    __device__ static void widen_part(const v4u32 &w, int, double *o) { widen(w, o); }
 };
 template <> struct vec16<float> {
     static constexpr int N = 4;
@@ -120,6 +124,8 @@ template <> struct vec16<float> {
 #pragma unroll
         for (int q = 0; q < 4; ++q) o[q] = (double)__uint_as_float(w[q]);
     }
+    static constexpr int P = 4;
+    __device__ static void widen_part(const v4u32 &w, int, double *o) { widen(w, o); }
 };
 template <> struct vec16<uint16_t> {                 // bfloat16
     static constexpr int N = 8;
@@ -139,6 +145,14 @@ template <> struct vec16<uint16_t> {                 // bfloat16
             o[2 * q + 1] = (double)bf16_to_f32((uint16_t)(w[q] >> 16));
         }
     }
+    static constexpr int P = 4;
+    __device__ static void widen_part(const v4u32 &w, int p, double *o) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            o[2 * q] = (double)bf16_to_f32((uint16_t)(w[2 * p + q] & 0xFFFFu));
+            o[2 * q + 1] = (double)bf16_to_f32((uint16_t)(w[2 * p + q] >> 16));
+        }
+    }
 };
 
 template <> struct vec16<uint8_t> {                  // FP8 E4M3
@@ -152,6 +166,8 @@ template <> struct vec16<uint8_t> {                  // FP8 E4M3
 #pragma unroll
         for (int q = 0; q < 4; ++q) e4m3x4_to_f64(w[q], o + 4 * q);
     }
+    static constexpr int P = 4;
+    __device__ static void widen_part(const v4u32 &w, int p, double *o) { e4m3x4_to_f64(w[p], o); }
 };
 
 

@@ -402,38 +402,26 @@ __global__ __launch_bounds__(kThreads) void k_encode_finish(FinSide<TC> x, FinSi
     }
 }
 
+constexpr int kRowThreads = 512;       // 8 waves
 // Per-row statistic of X[i, 0:k), one wave per row (grid-stride over rows),
 // 16-byte loads, eight in flight per lane, kept as raw words until each is
 // widened and summed in column order (the statistics are listed above the
-// encode kernels).  With ROW_W the weights sit in LDS as binary32, permuted so
-// that the lanes of a wave read consecutive words: lane L needs w[l0 + q] with
-// l0 = 64 V c + V L (chunk c of 64 V columns), stored at 64 V c + 64 q + L.
-constexpr int64_t kRowWMaxK = 16384;   // ROW_W keeps w (as binary32, 64 KB) in LDS up to this k
-constexpr int kRowThreads = 512;       // 8 waves share one copy of w
-// The rows of one block for a statistic fixed at compile time (WLDS: ROW_W
-// with the weights in LDS, permuted as above).
-template <typename T, int MODE, bool WLDS, bool NT>
+// encode kernels).
+template <typename T, int MODE, bool NT>
 __device__ __attribute__((always_inline)) inline void row_stats_rows(const T *X, int64_t ld, int64_t rows, int64_t k,
-                                                                     const double *w, const float *wsh, double *out,
-                                                                     int64_t blk, int64_t nblk) {
+                                                                     double *out, int64_t blk, int64_t nblk) {
+    static_assert(MODE != ROW_W, "weighted rows: row_w_rows");
     constexpr int V = vec16<T>::N;
     constexpr int NW = kRowThreads / kWave;
-    constexpr int64_t CH = (int64_t)kWave * V;
+    constexpr int64_t step = (int64_t)kWave * V;
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    auto term = [&](const double *v, int64_t l0, double &acc) {
-        const float *wc = wsh + (l0 / CH) * CH + lane;  // this lane's weights of l0's chunk, stride kWave
+    auto term = [&](const double *v, double &acc) {
 #pragma unroll
-        for (int q = 0; q < V; ++q) {
-            const double v2 = v[q] * v[q];
-            if constexpr (MODE == ROW_W) acc += v2 * (WLDS ? (double)wc[q * kWave] : w[l0 + q]);
-            else if constexpr (MODE == ROW_L4SQ) acc += v2 * v2;
-            else acc += v2;
-        }
+        for (int q = 0; q < V; ++q) acc += row_term(MODE, v[q], 0.0);
     };
     for (int64_t i = blk * NW + wave; i < rows; i += nblk * NW) {
         const T *row = X + i * ld;
         double acc = 0.0;
-        constexpr int64_t step = CH;
         int64_t l0 = (int64_t)lane * V;
         for (; l0 + 7 * step < k; l0 += 8 * step) {
             v4u32 raw[8];
@@ -443,16 +431,129 @@ __device__ __attribute__((always_inline)) inline void row_stats_rows(const T *X,
             for (int u = 0; u < 8; ++u) {
                 double v[V];
                 vec16<T>::widen(raw[u], v);
-                term(v, l0 + u * step, acc);
+                term(v, acc);
             }
         }
         for (; l0 < k; l0 += step) {
             double v0[V];
             vec16<T>::load(row + l0, v0);
-            term(v0, l0, acc);
+            term(v0, acc);
         }
         acc = wave_sum(acc);
-        if (lane == 0) out[i] = MODE == ROW_W ? acc : sqrt(acc);
+        if (lane == 0) out[i] = sqrt(acc);
+    }
+}
+
+// ROW_W, sum_l x_l^2 w_l: the weights stay binary64 -- they are sums of squares,
+// which leave binary32's range for operands of 2^64 and beyond, or 2^-75 and
+// below.  A block stages kWSlab of them in LDS at a time (32 KB; any k),
+// permuted so that the lanes of a wave read consecutive words: lane L needs
+// w[l0 + q] with l0 = 64 V c + V L (chunk c of 64 V columns), stored at
+// 64 V c + 64 q + L.  One slab that holds all of k is staged once for all of the
+// block's rows; otherwise the next slab's words are requested a slab ahead.  A
+// wave takes R rows together and U chunks at a time, the next ones requested
+// before these are summed; per row the terms are added in column order per lane,
+// then by the butterfly.  HBM-bound; the weights' reads of LDS are shared by the
+// R rows.  Whole encodes (us, binary32 weights of all of k in LDS and a row per
+// wave against this): bfloat16 16384 x 16384 twice 335 and 331, FP8 8192 x 8192
+// twice 100 and 95, binary32 8192 and 4096 x 16384 265 and 255, bfloat16 3000
+// and 5003 x 2056 29.6 and 28.5; 300 and 300 x 16384, four slabs in turn for
+// few rows, 31.5 and 34.3.
+constexpr int kWSlab = 4096;
+// Rows per wave: four where they still give every CU two blocks, else two
+// (11077 and 2631 x 5456 binary32: 128 us with four, 123 with two; 16384 x 1000
+// and 2000 62 with two, 59 with four).
+constexpr int kRowWRows = 4, kRowWFewRows = 2;
+__host__ __device__ inline bool row_w_multi(int64_t rows) { return rows >= 16384; }
+template <typename T, int R, int U, bool NT>
+__device__ __attribute__((always_inline)) inline void row_w_rows(const T *X, int64_t ld, int64_t rows, int64_t k,
+                                                                 const double *w, double *wsh, double *out, int64_t blk,
+                                                                 int64_t nblk) {
+    constexpr int V = vec16<T>::N;
+    constexpr int NW = kRowThreads / kWave;
+    constexpr int CH = kWave * V, STEP = U * CH;
+    static_assert(kWSlab % STEP == 0, "whole steps in a slab");
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    // weights of one slab to LDS, each thread's words requested into wn before
+    constexpr int WT = kWSlab / kRowThreads;
+    double wn[WT];
+    auto request_w = [&](int64_t s) {
+#pragma unroll
+        for (int e = 0; e < WT; ++e) {
+            const int64_t l = s + e * kRowThreads + threadIdx.x;
+            wn[e] = l < k ? w[l] : 0.0;
+        }
+    };
+    auto stage_w = [&](int64_t s) {
+        const int lim = (int)min((k - s + CH - 1) / CH * CH, (int64_t)kWSlab);
+#pragma unroll
+        for (int e = 0; e < WT; ++e) {
+            const int l = e * kRowThreads + threadIdx.x;
+            if (l < lim) wsh[l / CH * CH + l % V * kWave + l % CH / V] = wn[e];
+        }
+    };
+    const bool once = k <= kWSlab;                                       // one slab serves every row
+    request_w(0);
+    if (once) {
+        stage_w(0);
+        __syncthreads();
+    }
+    for (int64_t b0 = blk * NW * R; b0 < rows; b0 += nblk * NW * R) {    // every wave: the barriers are the block's
+        const int64_t i0 = b0 + wave * R;
+        const T *row[R];
+        double acc[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            row[r] = X + min(i0 + r, rows - 1) * ld + lane * V;          // rows past the last re-read it (not stored)
+            acc[r] = 0.0;
+        }
+        auto request = [&](v4u32 (&raw)[U][R], int64_t s) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (s + u * CH + lane * V < k) raw[u][r] = load_raw<NT, v4u32>(row[r] + s + u * CH);
+        };
+        v4u32 next[U][R];
+        request(next, 0);
+        for (int64_t s = 0; s < k; s += STEP) {
+            v4u32 raw[U][R];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int r = 0; r < R; ++r) raw[u][r] = next[u][r];
+            if (s + STEP < k) request(next, s + STEP);
+            if (!once && s % kWSlab == 0) {
+                __syncthreads();                                         // every wave is done with the last slab
+                stage_w(s);
+                request_w(s + kWSlab < k ? s + kWSlab : 0);              // the next, or the next rows' first
+                __syncthreads();
+            }
+            const double *ws = wsh + s % kWSlab + lane;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (s + u * CH + lane * V >= k) break;
+                constexpr int P = vec16<T>::P;
+#pragma unroll
+                for (int p = 0; p < V / P; ++p) {
+                    double wq[P];
+#pragma unroll
+                    for (int q = 0; q < P; ++q) wq[q] = ws[u * CH + (p * P + q) * kWave];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        double v[P];
+                        vec16<T>::widen_part(raw[u][r], p, v);
+#pragma unroll
+                        for (int q = 0; q < P; ++q) acc[r] += row_term(ROW_W, v[q], wq[q]);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            acc[r] = wave_sum(acc[r]);
+            if (lane == 0 && i0 + r < rows) out[i0 + r] = acc[r];
+        }
     }
 }
 
@@ -500,9 +601,8 @@ __device__ inline void tail_row(const EncJob &o, int64_t i) {
 }
 
 template <typename T, typename TC, bool NT>
-__global__ __launch_bounds__(kRowThreads) void k_encode_jobs(EncJobs jobs) {
-    constexpr int64_t CH = (int64_t)kWave * vec16<T>::N;   // columns per chunk (one 16-byte load per lane)
-    extern __shared__ float wsh[];                     // whole chunks of k for a ROW_W job with k <= kRowWMaxK
+__global__ __launch_bounds__(kRowThreads, 4) void k_encode_jobs(EncJobs jobs) {
+    extern __shared__ double wsh[];                    // a ROW_W job's weights: kWSlab, or k if less
     int64_t blk = blockIdx.x;
     int q = 0;
     while (q + 1 < jobs.n && blk >= jobs.j[q].blocks) blk -= jobs.j[q++].blocks;
@@ -510,19 +610,14 @@ __global__ __launch_bounds__(kRowThreads) void k_encode_jobs(EncJobs jobs) {
     switch (o.kind) {
     case JOB_ROWS: {
         const T *X = (const T *)o.X;
-        if (o.mode == ROW_W && o.k <= kRowWMaxK) {
-            for (int64_t l = threadIdx.x; l < o.k; l += kRowThreads) {
-                const int64_t c = l / CH, e = l - c * CH;
-                wsh[c * CH + (e % vec16<T>::N) * kWave + e / vec16<T>::N] = (float)o.w[l];
-            }
-            __syncthreads();
-            row_stats_rows<T, ROW_W, true, NT>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
-        } else if (o.mode == ROW_W) {
-            row_stats_rows<T, ROW_W, false, NT>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
+        if (o.mode == ROW_W) {
+            // four loads and the next four in flight per lane either way
+            if (row_w_multi(o.rows)) row_w_rows<T, kRowWRows, 1, NT>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
+            else row_w_rows<T, kRowWFewRows, 2, NT>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
         } else if (o.mode == ROW_L4SQ) {
-            row_stats_rows<T, ROW_L4SQ, false, NT>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
+            row_stats_rows<T, ROW_L4SQ, NT>(X, o.ld, o.rows, o.k, o.out, blk, o.blocks);
         } else {
-            row_stats_rows<T, ROW_L2, false, NT>(X, o.ld, o.rows, o.k, o.w, wsh, o.out, blk, o.blocks);
+            row_stats_rows<T, ROW_L2, NT>(X, o.ld, o.rows, o.k, o.out, blk, o.blocks);
         }
         break;
     }
@@ -557,15 +652,12 @@ struct JobList {
         a.j[a.n++] = EncJob{kind, mode, (unsigned)nblk, X, ld, rows, k, w, out};
         blocks += (unsigned)nblk;
     }
-    // With LDS-staged weights a block serves many rows.
     template <typename T> void rows(const T *X, int64_t ld, int64_t rows, int64_t k, int mode, const double *w,
                                     double *out) {
-        constexpr int NW = kRowThreads / kWave;
         constexpr int64_t CH = (int64_t)kWave * vec16<T>::N;   // the permuted weights fill whole chunks
-        static_assert(kRowWMaxK % CH == 0, "whole chunks within the LDS limit");
-        const bool wlds = mode == ROW_W && k <= kRowWMaxK;
-        if (wlds) lds = std::max(lds, sizeof(float) * (size_t)((k + CH - 1) / CH * CH));
-        add(JOB_ROWS, mode, std::min<int64_t>((rows + NW - 1) / NW, wlds ? 512 : 65536), X, ld, rows, k, w, out);
+        if (mode == ROW_W) lds = std::max(lds, sizeof(double) * (size_t)std::min<int64_t>((k + CH - 1) / CH * CH, kWSlab));
+        const int64_t per_block = kRowThreads / kWave * (mode != ROW_W ? 1 : row_w_multi(rows) ? kRowWRows : kRowWFewRows);
+        add(JOB_ROWS, mode, std::min<int64_t>((rows + per_block - 1) / per_block, mode == ROW_W ? 512 : 65536), X, ld, rows, k, w, out);
     }
     void sums(const double *X, int64_t ld, int64_t rows, int64_t n, int mode, double *out) {
         add(JOB_SUM, mode, (rows + kRowThreads / 8 - 1) / (kRowThreads / 8), X, ld, rows, n, nullptr, out);
