@@ -31,7 +31,7 @@ namespace {
 constexpr int kT = 256;
 constexpr int kW = 64;
 constexpr int kRowsPerIter = 64;        // row statistics: rows per block iteration (16 per wave)
-constexpr int kWLdsMax = 8192;          // row statistics: weights staged in LDS up to this k
+constexpr int kWLdsMax = 4096;          // row statistics: so many binary64 weights are staged in LDS (32 KB)
 
 struct BatchDesc {
     int64_t m, n, k, br, bc, lda, ldb, ldc, M, N, Gr, Gc;
@@ -368,41 +368,52 @@ __global__ __launch_bounds__(kT) void kb_encode2(const BatchDesc *__restrict__ d
 __device__ inline int64_t pad_to(int64_t x, int64_t q) { return (x + q - 1) / q * q; }
 
 // One row's statistic by a group of 16 lanes (lane16 = lane % 16).  U 16-byte
-// loads per lane are in flight, kept as raw words until they are summed.
+// loads per lane are in flight, kept as raw words until they are summed.  The
+// weights are sums of squares and stay binary64 (operands of 2^64 and beyond, or
+// 2^-75 and below, take them out of binary32's range): wsh holds the first
+// kWLdsMax of them, the rest are read from memory (16 problems of 1024 x 1024 x
+// 8192, b = 1: the whole encode 634 us with 8192 binary32 weights in LDS, 617
+// here, 739 with all of them read from memory).
 template <typename T, int MODE>   // MODE 0: sum x^4 -> sqrt; 1: sum x^2 w; 2: sum x^2 -> sqrt
-__device__ inline double row_stat(const G<T> *row, int64_t k, const float *wsh, const G<double> *wg, int lane16) {
+__device__ inline double row_stat(const G<T> *row, int64_t k, const double *wsh, const G<double> *wg, int lane16) {
     constexpr int V = 16 / (int)sizeof(T), U = 8;
+    static_assert(kWLdsMax % (U * 16 * V) == 0, "whole steps from LDS");
     double acc = 0.0;
-    for (int64_t l0 = (int64_t)lane16 * V; l0 < k; l0 += U * 16 * V) {
-        v4u_ raw[U];
+    auto terms = [&](int64_t l0, int64_t k1, auto weight) {
+        for (; l0 < k1; l0 += U * 16 * V) {
+            v4u_ raw[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t l = l0 + (int64_t)u * 16 * V;
-            if (l < k) raw[u] = *(const G<v4u_> *)(row + l);
-        }
-        // the same order of terms per lane as one load at a time
+            for (int u = 0; u < U; ++u) {
+                const int64_t l = l0 + (int64_t)u * 16 * V;
+                if (l < k1) raw[u] = *(const G<v4u_> *)(row + l);
+            }
+            // the same order of terms per lane as one load at a time
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t l = l0 + (int64_t)u * 16 * V;
-            if (l < k) {
+            for (int u = 0; u < U; ++u) {
+                const int64_t l = l0 + (int64_t)u * 16 * V;
+                if (l < k1) {
 #pragma unroll
-                for (int e = 0; e < V; ++e) {
-                    const double x = chunk_elem<T>(raw[u], e);
-                    double x2 = x * x;
-                    if (MODE == 1) acc += x2 * (wsh ? (double)wsh[l + e] : wg[l + e]);
-                    else if (MODE == 0) acc += x2 * x2;
-                    else acc += x2;
+                    for (int e = 0; e < V; ++e) {
+                        const double x = chunk_elem<T>(raw[u], e);
+                        double x2 = x * x;
+                        if (MODE == 1) acc += x2 * weight(l + e);
+                        else if (MODE == 0) acc += x2 * x2;
+                        else acc += x2;
+                    }
                 }
             }
         }
-    }
+    };
+    const int64_t l0 = (int64_t)lane16 * V, k1 = MODE == 1 ? min(k, (int64_t)kWLdsMax) : k;
+    terms(l0, k1, [&](int64_t l) { return wsh[l]; });
+    if (MODE == 1 && k > k1) terms(k1 + l0, k, [&](int64_t l) { return wg[l]; });
     for (int off = 8; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kW);
     return MODE == 1 ? acc : sqrt(acc);
 }
 
 // 64 rows per block iteration: 16 per wave, 4 at a time (16 lanes per row).
 __global__ __launch_bounds__(kT) void kb_rowstats(const BatchDesc *__restrict__ d, int count, int64_t total) {
-    __shared__ float wsh[kWLdsMax];
+    __shared__ double wsh[kWLdsMax];
     const int lane = threadIdx.x % kW, wave = threadIdx.x / kW, lane16 = lane % 16;
     Walk<&BatchDesc::s_rows, kRowsPerIter> wk(d, count, total);
     const G<double> *staged = nullptr;                 // the weights wsh holds
@@ -415,14 +426,12 @@ __global__ __launch_bounds__(kT) void kb_rowstats(const BatchDesc *__restrict__ 
         const int64_t r0 = seg == 0 ? q0 : (seg == 1 ? q0 - pa : q0 - pa - pb);
         const bool use_w = seg == 0 ? D.bc == 1 : (seg == 1 ? D.br == 1 : false);
         const G<double> *wg = seg == 0 ? gp(D.grpB) : gp(D.grpA);
-        const bool wlds = use_w && D.k <= kWLdsMax;
-        if (wlds && staged != wg) {
+        if (use_w && staged != wg) {
             __syncthreads();                           // every wave is done with the previous weights
-            for (int64_t l = threadIdx.x; l < D.k; l += kT) wsh[l] = (float)wg[l];
+            for (int64_t l = threadIdx.x; l < min(D.k, (int64_t)kWLdsMax); l += kT) wsh[l] = wg[l];
             __syncthreads();
             staged = wg;
         }
-        const float *ws = wlds ? wsh : nullptr;
 #pragma unroll
         for (int e = 0; e < kRowsPerIter / 16; ++e) {
             const int64_t r = r0 + wave * (kRowsPerIter / 4) + e * 4 + lane / 16;
@@ -431,20 +440,20 @@ __global__ __launch_bounds__(kT) void kb_rowstats(const BatchDesc *__restrict__ 
             if (seg == 0) {
                 if (r < D.br) {
                     const G<float> *row = gp(D.acs) + r * D.k;
-                    out = use_w ? row_stat<float, 1>(row, D.k, ws, wg, lane16)
-                                : row_stat<float, 0>(row, D.k, ws, wg, lane16);
+                    out = use_w ? row_stat<float, 1>(row, D.k, wsh, wg, lane16)
+                                : row_stat<float, 0>(row, D.k, wsh, wg, lane16);
                     dst = gp(D.qr) + D.m + r;
                 }
             } else if (seg == 1) {
                 if (r < nb) {
                     const G<uint16_t> *row = gp(D.Bt) + r * D.ldb;
-                    out = use_w ? row_stat<uint16_t, 1>(row, D.k, ws, wg, lane16)
-                                : row_stat<uint16_t, 0>(row, D.k, ws, wg, lane16);
+                    out = use_w ? row_stat<uint16_t, 1>(row, D.k, wsh, wg, lane16)
+                                : row_stat<uint16_t, 0>(row, D.k, wsh, wg, lane16);
                     dst = gp(D.qc) + r;
                 } else if (r < nb + D.bc) {
                     const G<float> *row = gp(D.bcs) + (r - nb) * D.k;
-                    out = use_w ? row_stat<float, 1>(row, D.k, ws, wg, lane16)
-                                : row_stat<float, 0>(row, D.k, ws, wg, lane16);
+                    out = use_w ? row_stat<float, 1>(row, D.k, wsh, wg, lane16)
+                                : row_stat<float, 0>(row, D.k, wsh, wg, lane16);
                     dst = gp(D.qc) + D.n + (r - nb);
                 }
             } else {

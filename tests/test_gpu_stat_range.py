@@ -89,3 +89,35 @@ def test_thresholds_and_decisions_far_from_one(dev, orc, case, ea):
         assert abs(tau - tc[r, jj]) <= 1e-10 * tc[r, jj], (r, jj, tau, tc[r, jj])
     for ii, c, _, tau in rep.flags_r():
         assert abs(tau - tr[ii, c]) <= 1e-10 * tr[ii, c], (ii, c, tau, tr[ii, c])
+
+
+@pytest.mark.parametrize("ea", [70, -70])
+def test_batched_thresholds_far_from_one(dev, orc, ea):
+    """The same of the batched products: every threshold of every problem."""
+    print(f"[case] batched statistics at scale 2^{ea}", flush=True)
+    shapes = [(130, 96, 64, 1, 1), (96, 130, 520, 1, 1), (64, 60, 2048, 1, 1), (48, 40, 4616, 1, 1), (60, 64, 136, 4, 1),
+              (64, 60, 136, 1, 4)]
+    bt = abft.Batch(shapes, device=dev, lam=10.0)
+    host = []
+    for q, (m, n, k, _, _) in enumerate(shapes):
+        A = np.ldexp(synth.uniform(SEED + q, synth.STREAM_A, m, k, np.float32), ea).astype(np.float32)
+        Bt = np.ldexp(synth.uniform(SEED + q, synth.STREAM_B, n, k, np.float32), -ea).astype(np.float32)
+        Bt[n // 2, ::3] = 0.0
+        A[m // 2, ::5] = 0.0
+        bt.A32[q].copy_(torch.from_numpy(A))
+        bt.Bt32[q].copy_(torch.from_numpy(Bt))
+        host.append(tuple(orc.bf16_bits_to_f64(orc.to_bf16_bits(X)).astype(np.float64) for X in (A, Bt)))
+    abft.batch_quantize_encode(bt.plan)
+    abft.batch_gemm(bt.plan)
+    abft.batch_verify(bt.plan)
+    assert bt.fetch_reports() == []
+    for q, (m, n, k, br, bc) in enumerate(shapes):
+        A, Bt = host[q]
+        Af, Bf = orc.encode(A, np.ascontiguousarray(Bt.T), br, bc, store_f32=True)
+        Cf = bt.C[q].cpu().numpy().astype(np.float64)
+        tc, tr = orc.tau_stat(Af, Bf, m, n, br, bc, T=k / 4.0, s_store=2.0, lam=10.0, Cf=Cf, T_c=k / 4.0)
+        tau_c = torch.zeros(br, n + bc, dtype=torch.float64, device=dev)
+        tau_r = torch.zeros(m + br, bc, dtype=torch.float64, device=dev)
+        abft.batch_thresholds(bt.plan, q, tau_c, tau_r)
+        for got, want in ((tau_c.cpu().numpy(), tc), (tau_r.cpu().numpy(), tr)):
+            assert np.all(np.abs(got - want) <= 1e-10 * want), (q, np.max(np.abs(got - want) / want))
