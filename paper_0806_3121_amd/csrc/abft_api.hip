@@ -39,7 +39,7 @@ EncSplit enc_split(int64_t R, int64_t b, int64_t k, int V) {
     // 64 lanes read 1 KB of a row at once; where that leaves over a tenth of the lanes past the last column, 16 do
     e.cw = (kv % 64 == 0 || kv >= 640) ? 64 : 16;
     const int64_t rw = 256 / e.cw;
-    e.strips = (kv + e.cw - 1) / e.cw;
+    e.strips = std::max<int64_t>(1, (kv + e.cw - 1) / e.cw);   // k below one vector: sized, never encoded
     const int64_t direct = e.strips * ((b + rw - 1) / rw);
     // whole residues per lane where few groups or enough residues make it short, else enough partitions for
     // about 16 blocks per CU, each with at least four rows per row lane (what a lane requests together)
