@@ -12,7 +12,12 @@
 // ones are summed: with a step's loads, wait and sums in turn the rate stays
 // at 5 TB/s however many rows share a wave, with the next step in flight it is
 // 6.5 (2.1 GB binary64 operand against two rows, four rows per wave: 401 us
-// and 330).
+// and 330).  With a short k the sums over the lanes and the waves in flight
+// count instead: the sums go by a reduce-scatter and widened values are held a
+// part at a time (whole products, us, butterflies and whole chunks widened
+// against this: FP8 215241 x 5 x 16 79 and 53, FP8 blocks of 512 362312 x 512 x
+// 16 42034 and 27672, bfloat16 342573 x 62 x 16 106 and 79; 4096 x 4096 x 1024
+// FP8 blocks of 16 83 and 74).
 #pragma once
 
 #include <type_traits>
@@ -133,35 +138,55 @@ __device__ __attribute__((always_inline)) inline void sliver_rows(const SliverJo
                 get_x(nx, k0 + UK * 64 * V);
                 if constexpr (PFY) get_y(ny, k0 + UK * 64 * V);
             }
+            // a part of four (binary64: two) k at a time, so that few widened values are held
+            constexpr int P = vec16<TX>::P;
+            static_assert(P == VY && VX % P == 0, "a part is a chunk of Y");
 #pragma unroll
             for (int c = 0; c < UK; ++c) {
                 if (k0 + c * 64 * V >= j.K) break;
-                double xv[NR][V];
 #pragma unroll
-                for (int r = 0; r < NR; ++r)
+                for (int p = 0; p < V / P; ++p) {
+                    double xv[NR][P];
 #pragma unroll
-                    for (int q = 0; q < V / VX; ++q) vec16<TX>::widen(xw[c][r][q], xv[r] + q * VX);
+                    for (int r = 0; r < NR; ++r) vec16<TX>::widen_part(xw[c][r][p * P / VX], p * P % VX / P, xv[r]);
 #pragma unroll
-                for (int y = 0; y < NY; ++y) {
-                    double yv[V];
+                    for (int y = 0; y < NY; ++y) {
+                        double yv[P];
+                        vec16<TY>::widen(yw[c][y][p], yv);
 #pragma unroll
-                    for (int q = 0; q < V / VY; ++q) vec16<TY>::widen(yw[c][y][q], yv + q * VY);
+                        for (int r = 0; r < NR; ++r)
 #pragma unroll
-                    for (int r = 0; r < NR; ++r)
-#pragma unroll
-                        for (int q = 0; q < V; ++q) acc[r][y] = fma(xv[r][q], yv[q], acc[r][y]);
+                            for (int q = 0; q < P; ++q) acc[r][y] = fma(xv[r][q], yv[q], acc[r][y]);
+                    }
                 }
             }
         }
+        // the NR NY sums over the lanes by a reduce-scatter: each exchange halves the sums a lane holds until one
+        // is left, then a butterfly within the lanes that share it -- per sum the same additions as a butterfly
+        // over the wave, with about a fifth of the exchanges for eight sums (what a short k spends its time on)
+        constexpr int NS = NR * NY;
+        static_assert((NS & (NS - 1)) == 0 && NS <= 64, "a power of two");
+        double v[NS];
 #pragma unroll
         for (int r = 0; r < NR; ++r)
 #pragma unroll
-            for (int y = 0; y < NY; ++y) {
-                double v = acc[r][y];
-                for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-                if (lane == 0 && u0 + r < j.U && y < j.R)
-                    store_out<TC>(j.out + (u0 + r) * j.ou + y * j.os, scale * v, accumulate);
+            for (int y = 0; y < NY; ++y) v[r * NY + y] = acc[r][y];
+#pragma unroll
+        for (int off = 32, h = NS / 2; off > 0; off >>= 1, h >>= 1) {
+            if (h > 0) {
+                const bool up = lane & off;
+#pragma unroll
+                for (int e = 0; e < h; ++e) {
+                    const double keep = up ? v[e + h] : v[e], send = up ? v[e] : v[e + h];
+                    v[e] = keep + __shfl_xor(send, off, 64);
+                }
+            } else {
+                v[0] += __shfl_xor(v[0], off, 64);
             }
+        }
+        const int e = lane / (64 / NS), r = e / NY, y = e % NY;
+        if (lane % (64 / NS) == 0 && u0 + r < j.U && y < j.R)
+            store_out<TC>(j.out + (u0 + r) * j.ou + y * j.os, scale * v[0], accumulate);
     }
 }
 
@@ -202,7 +227,7 @@ __device__ __attribute__((always_inline)) inline void sliver_launch(const Sliver
     sliver_rows<TX, TY, TC, NR, NY, UK, NT>(first ? a : b, scale, x.accumulate != 0, first ? blk : blk - a.blocks);
 }
 template <typename TX, typename TY, typename TC, int NY, bool NT>
-__global__ __launch_bounds__(kSliverThreads) void k_sliver(SliverJob<TX, TY, TC> a, SliverJob<TX, TY, TC> b,
+__global__ __launch_bounds__(kSliverThreads, sizeof(TX) == 1 && NY == 8 ? 2 : 4) void k_sliver(SliverJob<TX, TY, TC> a, SliverJob<TX, TY, TC> b,
                                                           SliverExtra x) {
     constexpr int V = vec16<TX>::N > vec16<TY>::N ? vec16<TX>::N : vec16<TY>::N;
     // chunks of k per lane in a step, fewer where more rows of Y hold registers
@@ -218,11 +243,16 @@ __global__ __launch_bounds__(kSliverThreads) void k_sliver(SliverJob<TX, TY, TC>
 // types four rows and one chunk (two rows: binary32 16384 x 16384 169 us against
 // 163, FP8 16384 x 16384 twice 138 against 120, bfloat16 16384 x 1024 twice 25
 // against 22).
+// A k of a chunk or two leaves nothing to keep in flight but rows: four rows
+// then for binary64 too (whole product 111487 x 23 x k, two rows and four: k 72
+// 56 and 38 us, 200 74 and 68, 256 81 and 79, 384 125 and 126, 512 167 and 178;
+// 349475 x 29 x 8 123 and 74).
 template <typename TX> constexpr int kSliverRows = sizeof(TX) == 8 ? 2 : 4;
-template <typename TX, typename TY, typename TC, int NY, bool NT>
-__global__ __launch_bounds__(kSliverThreads) void k_sliver1(SliverJob<TX, TY, TC> a, SliverJob<TX, TY, TC> b,
-                                                           SliverExtra x) {
-    sliver_launch<TX, TY, TC, kSliverRows<TX>, NY, sizeof(TX) == 8 ? 4 : 1, NT>(a, b, x);
+template <typename TX> inline bool sliver_short(int64_t K) { return sizeof(TX) == 8 && K <= 256; }
+template <typename TX, typename TY, typename TC, int NY, bool NT, int NR>
+__global__ __launch_bounds__(kSliverThreads, sizeof(TX) == 8 ? 1 : (NY == 1 ? 4 : 3)) void k_sliver1(
+    SliverJob<TX, TY, TC> a, SliverJob<TX, TY, TC> b, SliverExtra x) {
+    sliver_launch<TX, TY, TC, NR, NY, NR == 2 ? 4 : 1, NT>(a, b, x);
 }
 inline bool sliver_multirow(int64_t R, int64_t U) { return R <= 2 && U >= 16384; }
 
@@ -235,9 +265,9 @@ inline int slivers(SliverJob<TX, TY, TC> a, const SliverJob<TX, TY, TC> *b, cons
     auto run = [&](Job u, Job v, bool with_v, const SliverExtra &e) {
         if (!with_v) { v = u; v.blocks = 0; }
         const int64_t per_block = kSliverThreads / 64;
-        const bool multi = sliver_multirow(u.R, u.U);
+        const bool multi = sliver_multirow(u.R, u.U), brief = sliver_short<TX>(u.K);
         auto blocks = [&](const Job &j) {
-            const int64_t waves = multi ? (j.U + kSliverRows<TX> - 1) / kSliverRows<TX> : j.U;
+            const int64_t rows = brief ? 4 : kSliverRows<TX>, waves = multi ? (j.U + rows - 1) / rows : j.U;
             return (unsigned)std::min<int64_t>((waves + per_block - 1) / per_block, 4096);
         };
         u.blocks = blocks(u);
@@ -249,7 +279,10 @@ inline int slivers(SliverJob<TX, TY, TC> a, const SliverJob<TX, TY, TC> *b, cons
             constexpr int NY = decltype(ny)::value;
             constexpr bool NT = decltype(st)::value;
             if (multi) {
-                if constexpr (NY <= 2) k_sliver1<TX, TY, TC, NY, NT><<<grid, kSliverThreads, 0, s>>>(u, v, e);
+                if constexpr (NY <= 2) {
+                    if (brief) k_sliver1<TX, TY, TC, NY, NT, 4><<<grid, kSliverThreads, 0, s>>>(u, v, e);
+                    else k_sliver1<TX, TY, TC, NY, NT, kSliverRows<TX>><<<grid, kSliverThreads, 0, s>>>(u, v, e);
+                }
             } else {
                 k_sliver<TX, TY, TC, NY, NT><<<grid, kSliverThreads, 0, s>>>(u, v, e);
             }
