@@ -269,8 +269,15 @@ static int protected_product_lowp(const abft_problem *p, const Geom &g, const ty
     float *Crow = C + g.m * p->ldc;
     SliverExtra x = sliver_extra(scale_exp, false);
     // corner C_f[m + r, n + c]
-    x.Yr = Acs; x.Yc = Bcs; x.K = g.k; x.nc = g.bc; x.out = Crow + g.n; x.ldo = p->ldc;
-    x.blocks = (unsigned)(g.br * g.bc);
+    if (g.br * g.bc >= kCornerTiled) {
+        auto j = sliver_job<float, float, float>(Bcs, g.k, g.bc, Acs, g.k, kCornerRows, g.k, Crow + g.n, 1, p->ldc);
+        j.blocks = (unsigned)std::min<int64_t>((g.bc + 15) / 16, 4096);      // four waves of four columns each
+        const unsigned pieces = (unsigned)std::min<int64_t>((g.br + kCornerRows - 1) / kCornerRows, 4096);
+        k_corner<<<dim3(j.blocks, pieces), kSliverThreads, 0, s>>>(j, g.br, scale_exp);
+    } else {
+        x.Yr = Acs; x.Yc = Bcs; x.K = g.k; x.nc = g.bc; x.out = Crow + g.n; x.ldo = p->ldc;
+        x.blocks = (unsigned)(g.br * g.bc);
+    }
     if (tag) { x.tag = tag->dst; x.key = tag->key(); tag->dst = nullptr; }
     // C_f[m + r, j], j < n, and C_f[i, n + c], i < m
     const auto cols = sliver_job<E, float, float>(A, p->lda, g.m, Bcs, g.k, g.bc, g.k, C + g.n, p->ldc, 1);

@@ -211,6 +211,27 @@ __device__ inline void sliver_corner(const SliverExtra &x, double scale, int64_t
     }
 }
 
+// The corner of wide checksum blocks in a launch of its own: a wave takes four
+// columns and four rows, so that the checksum rows are read from L2 half a row
+// per entry instead of two.  From kCornerTiled entries on: fewer are spread over
+// more of the device a block each, beside the carried rows and columns (us, the
+// whole bfloat16 product 4096 x 4096 x 2048 with checksum blocks of 64, 128, 256
+// and 1024, the corner by blocks 252 / 457 / 906 / 4478, by tiles 252 / 437 / 830
+// / 3294).
+constexpr int64_t kCornerTiled = 16384;
+constexpr int kCornerRows = 4;
+__global__ __launch_bounds__(kSliverThreads) void k_corner(SliverJob<float, float, float> j, int64_t rows,
+                                                          const int *scale_exp) {
+    const double scale = scale_exp ? ldexp(1.0, -(scale_exp[0] + scale_exp[1])) : 1.0;
+    for (int64_t r0 = (int64_t)blockIdx.y * kCornerRows; r0 < rows; r0 += (int64_t)gridDim.y * kCornerRows) {
+        SliverJob<float, float, float> p = j;
+        p.Y += r0 * j.ldy;
+        p.out += r0 * j.os;
+        p.R = (int)min((int64_t)kCornerRows, rows - r0);
+        sliver_rows<float, float, float, 4, kCornerRows, 1, false>(p, scale, false, blockIdx.x);
+    }
+}
+
 // One or two jobs (blocks [0, a.blocks), then b's), then the extras.
 template <typename TX, typename TY, typename TC, int NR, int NY, int UK, bool NT>
 __device__ __attribute__((always_inline)) inline void sliver_launch(const SliverJob<TX, TY, TC> &a,

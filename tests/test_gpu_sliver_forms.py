@@ -1,5 +1,6 @@
 """GPU test of the carried blocks' forms: every count of checksum rows a launch
-groups (1, 2, 4, 8 and a remainder), several operand rows per wave with k of one short
+groups (1, 2, 4, 8 and a remainder), the corner entry by entry and by tiles
+(ragged in both directions), several operand rows per wave with k of one short
 chunk and of more, in every element type.
 
 The operands hold integers in [-2, 2], so checksum sums, products and the
@@ -20,6 +21,8 @@ DT = {"f64": abft.ABFT_F64, "f32": abft.ABFT_F32, "bf16": abft.ABFT_BF16, "fp8":
 CASES = [(dt, 3 * b, 2 * c, k, b, c) for dt in ("f64", "f32", "bf16", "fp8")
          for b, c, k in ((1, 1, 16), (2, 3, 528), (3, 2, 272), (4, 8, 1040), (5, 7, 48), (8, 6, 2064))]
 CASES += [("bf16", 18, 34, 24, 9, 17), ("fp8", 34, 18, 1104, 17, 9)]                       # more than one group of eight
+CASES += [("bf16", 262, 260, 264, 131, 130), ("fp8", 130, 264, 48, 130, 132),              # corner by tiles
+          ("bf16", 6, 5500, 16, 3, 5500), ("fp8", 128, 128, 2064, 128, 128)]
 CASES += [("f64", 16400, 6, k, 2, 1) for k in (2, 128, 130, 256, 258)]                     # several rows per wave
 CASES += [("f32", 16390, 4, 20, 1, 2), ("bf16", 16389, 5, 8, 1, 1), ("fp8", 16400, 6, 32, 2, 2)]
 
