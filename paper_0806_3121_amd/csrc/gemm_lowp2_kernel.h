@@ -18,7 +18,7 @@
 //
 // Rows beyond M (columns beyond N) load a clamped valid row; they only feed
 // results that are not stored.  K must be a multiple of the slab (128 bytes);
-// other K use the half-slab ring of gemm_lowp_ring_kernel.h.
+// other K use the ring of gemm_lowp_ring_kernel.h.
 #pragma once
 
 #include "gemm_lowp_kernel.h"

@@ -88,7 +88,7 @@ static const TileChoice kF32Tiles[] = {
 
 // The data-part kernel and tile for an M x N x K product of element type E.
 struct MainPick {
-    bool direct;            // direct-to-LDS kernel with one barrier per slab (else register-staged / half-slab ring)
+    bool direct;            // direct-to-LDS kernel for whole slabs only in low precision (else register-staged / ring)
     const TileChoice *t;
 };
 // Whether an M x N x K product (K in slabs of BK) is picked from the direct
@@ -214,41 +214,58 @@ static int protected_product(const abft_problem *p, const Geom &g, const E *A, c
 }
 
 // bfloat16 / FP8 candidates, picked by rounds.  eff orders the tiles as measured
-// (us, 256x256 / 256x128 / 128x128 / 64x64): bfloat16 4096^3 106 / 132 / 149 / 246,
-// 3000 x 5003 x 2056 70 / 95 / 106 / 211, 2048^3 43 / 31 / 24 / 34, 440 x 11551 x 1832
-// 58 / 45 / 55 / 71, 1487 x 2294 x 1824 46 / 34 / 24 / 34, 861 x 765 x 4504
-// 124 / 93 / 64 / 27, 1024^3 23 / 15 / 11 / 8.0; FP8 3000 x 5003 x 2064
-// 47 / 60 / 63 / 113, 1570 x 3468 x 880 27 / 20 / 20 / 22, 2048^3 29 / 22 / 17 / 21,
-// 861 x 765 x 4512 50 / 44 / 34 / 16.  The 64 x 64 tile is not offered to a fused
-// epilogue, whose sums have no room for it, nor below eight slabs of k, where a
-// launch is mostly its start and stores (FP8 500 x 600 x 528: 10.9 us with either
-// small tile).
+// (us, 256x256 / 256x128 / 128x128 / 64x64): bfloat16 16384^3 6557 / 8428 / 7981 /
+// 17138, 8431 x 8116 x 8824 1272 / 1465 / 1522 / 3060, 3000 x 5003 x 2056
+// 66 / 81 / 84 / 171, 2048^3 43 / 32 / 26 / 28, 440 x 11551 x 1832 51 / 37 / 45 / 67,
+// 861 x 765 x 4504 108 / 70 / 51 / 26, 1024^3 24 / 18 / 12 / 11; FP8 3000 x 5003 x
+// 2064 44 / 52 / 53 / 95, 1570 x 3468 x 880 25 / 18 / 17 / 19, 2048^3
+// 27 / 22 / 16 / 17, 861 x 765 x 4512 51 / 37 / 28 / 15.  The 64 x 64 tile is not
+// offered to a fused epilogue, whose sums have no room for it.  Below eight slabs
+// of k, where a launch is mostly its start and stores, it is the tile of products
+// no wider than itself (bfloat16 299247 x 26 x 32: 19 us, 128x128 29, FP8 16 x
+// 289750 x 352: 24 and 33) and not offered to others (FP8 500 x 600 x 528: 10.9 us
+// with either small tile).
+// A whole number of rounds away the order moves with k and the rows' alignment by a
+// few percent only (68015 x 1008 x 752: 183 / 189 / 184); 128x128 needs three rounds
+// and more to come near its rate (4913 x 2276 x 2976: 93 us, 256x256 77).
 // When k is a multiple of the 128-byte slab the 256 x 256 tile runs in the kernel
-// with one barrier per slab (4096^3: 98 us against the ring's 106, 16384^3 6.4 ms
-// against 7.2); a masked last slab costs that one more registers than it has.
+// made for that (16384^3: 6472 us, 6421 in the ring).
 static const TileChoice kLowpTiles[] = {
-    {0, 256, 256, 1, 0.50}, {3, 256, 128, 1, 0.35}, {1, 128, 128, 2, 0.31}, {2, 64, 64, 4, 0.19},
+    {0, 256, 256, 1, 0.50}, {3, 256, 128, 1, 0.36}, {1, 128, 128, 2, 0.35}, {2, 64, 64, 4, 0.195},
 };
 static MainPick pick_main_lowp(int64_t elem_size, int64_t M, int64_t N, int64_t K, bool fused) {
     const int64_t slab = 128 / elem_size;
-    const TileChoice *t = &kLowpTiles[choose_rounds(kLowpTiles, fused || K < 8 * slab ? 3 : 4, M, N)];
+    const bool brief = K < 8 * slab;
+    if (brief && !fused && std::min(M, N) <= 64) return {false, &kLowpTiles[3]};
+    const TileChoice *t = &kLowpTiles[choose_rounds(kLowpTiles, fused || brief ? 3 : 4, M, N)];
     return {t->bm == 256 && t->bn == 256 && K % slab == 0, t};
 }
+// The ring's depth by what shares a CU: where the small tiles are no more than
+// the device holds at once with deep rings, four slabs in flight cover a lone
+// block's latency (bfloat16 861 x 765 x 4504 on 64x64: 26 us, two slabs 35; 2048^3 on
+// 128x128: 25.8 and 26.3); else two slabs and more blocks per CU (128 x 101760 x 2376
+// on 128x128: 169 us, four slabs 173; 336023 x 135 x 232 110 and 162).
 template <class Ops>
 static int gemm_main_lowp(const typename Ops::E *A, int64_t lda, const typename Ops::E *Bt, int64_t ldb, float *C,
                           int64_t ldc, int64_t M, int64_t N, int64_t K, const int *scale_exp, hipStream_t s,
                           EpiArgs *e = nullptr) {
     const MainPick pk = pick_main_lowp((int64_t)sizeof(typename Ops::E), M, N, K, e && e->pc);
     if (pk.direct) return launch_gemm_lowp2<Ops, 4>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
+    const int64_t tiles = ((M + pk.t->bm - 1) / pk.t->bm) * ((N + pk.t->bn - 1) / pk.t->bn);
     switch (pk.t->id) {
     case 0:
-        return launch_gemm_lowp<LowpRing<Ops, 256, 256, 4, 2, 1>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
+        return launch_gemm_lowp<LowpRing<Ops, 256, 256, 4, 2, 1, 2>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
     case 2:
-        return launch_gemm_lowp<LowpRing<Ops, 64, 64, 2, 2, 4>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
+        if (tiles <= 512)
+            return launch_gemm_lowp<LowpRing<Ops, 64, 64, 2, 2, 2, 4>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
+        return launch_gemm_lowp<LowpRing<Ops, 64, 64, 2, 2, 4, 2>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
     case 3:
-        return launch_gemm_lowp<LowpRing<Ops, 256, 128, 4, 2, 1>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
+        return launch_gemm_lowp<LowpRing<Ops, 256, 128, 4, 2, 1, 3>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
     default:
-        return launch_gemm_lowp<LowpRing<Ops, 128, 128, 2, 2, 2>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
+        if (tiles <= 256)
+            return launch_gemm_lowp<LowpRing<Ops, 128, 128, 2, 2, 1, 4>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s,
+                                                                        e);
+        return launch_gemm_lowp<LowpRing<Ops, 128, 128, 2, 2, 2, 2>>(A, lda, Bt, ldb, C, ldc, M, N, K, scale_exp, s, e);
     }
 }
 
