@@ -943,36 +943,46 @@ __device__ inline float fin_abs(float x) {
 }
 
 // One or both operands: blocks [0, nx) on x, the rest on y; each block's
-// maximum goes to its slot.  A wave takes runs of 2048 columns of a row, eight
-// loads in flight per lane and no division per load (one per element vector
-// held the pass at 3.5 TB/s).
+// maximum goes to its slot.  A load instruction takes 64 vectors of four columns:
+// a piece of one row, or several rows of a short k side by side (one row at a
+// time left most lanes idle: 379665 x 48 quantized in 121 us, 31 here); a wave
+// takes runs of eight, all in flight, with no division per load (one per element
+// vector held the pass at 3.5 TB/s).
 struct AmaxSide {
     const float *X;
     int64_t ldx, rows, k;
     float *out;
+    int shift;               // log2 of the lanes across a row
+    int64_t pieces, total;   // load instructions across a row; in all
 };
+constexpr int kAmaxRun = 8;
+static AmaxSide amax_side(const float *X, int64_t ldx, int64_t rows, int64_t k, float *out) {
+    int shift = 0;
+    while (shift < 6 && (int64_t(4) << shift) < k) ++shift;
+    const int64_t across = int64_t(4) << shift, pieces = (k + across - 1) / across, per = kWave >> shift;
+    return AmaxSide{X, ldx, rows, k, out, shift, pieces, (rows + per - 1) / per * pieces};
+}
 template <bool NT>
 __global__ __launch_bounds__(kThreads) void k_amax(AmaxSide x, AmaxSide y, unsigned nx) {
     typedef float v4 __attribute__((ext_vector_type(4)));
-    constexpr int U = 8;
-    constexpr int64_t RUN = (int64_t)kWave * 4 * U;
     __shared__ float sh[kThreads / kWave];
     const AmaxSide &o = blockIdx.x < nx ? x : y;
     const unsigned blk = blockIdx.x < nx ? blockIdx.x : blockIdx.x - nx, nblk = blockIdx.x < nx ? nx : gridDim.x - nx;
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    const int64_t runs = (o.k + RUN - 1) / RUN, total = o.rows * runs;
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int r = lane >> o.shift, c = (lane & ((1 << o.shift) - 1)) * 4;      // this lane's row and column of a piece
     float mx = 0.0f;
-    for (int64_t t = (int64_t)blk * (kThreads / kWave) + wave; t < total; t += (int64_t)nblk * (kThreads / kWave)) {
-        const int64_t i = t / runs, l0 = (t - i * runs) * RUN + lane * 4;
-        const float *row = o.X + i * o.ldx;
-        v4 v[U];
+    for (int64_t t = ((int64_t)blk * (kThreads / kWave) + wave) * kAmaxRun; t < o.total;
+         t += (int64_t)nblk * (kThreads / kWave) * kAmaxRun) {
+        int64_t g = t / o.pieces, p = t - g * o.pieces;                        // row group and piece of the next load
+        v4 v[kAmaxRun];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t l = l0 + u * kWave * 4;
-            v[u] = l < o.k ? load_raw<NT, v4>(row + l) : v4{0.f, 0.f, 0.f, 0.f};
+        for (int u = 0; u < kAmaxRun; ++u) {
+            const int64_t i = (g << (6 - o.shift)) + r, l = (p << (o.shift + 2)) + c;
+            v[u] = i < o.rows && l < o.k ? load_raw<NT, v4>(o.X + i * o.ldx + l) : v4{0.f, 0.f, 0.f, 0.f};
+            if (++p == o.pieces) { p = 0; ++g; }
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < kAmaxRun; ++u)
             mx = fmaxf(mx, fmaxf(fmaxf(fin_abs(v[u][0]), fin_abs(v[u][1])), fmaxf(fin_abs(v[u][2]), fin_abs(v[u][3]))));
     }
     for (int off = kWave / 2; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
@@ -1026,10 +1036,11 @@ static void scale_exponents(const abft_problem *p, int which, const float *X, in
     // the quantizing pass reads the operands again: kept in cache where both fit
     const bool nt = streams((p->m + p->n) * p->k * 4);
     auto side = [&](int w, const float *P, int64_t ld) {
-        return AmaxSide{P, ld, w == 0 ? p->m : p->n, p->k, amax + w * kAmaxBlocks};
+        return amax_side(P, ld, w == 0 ? p->m : p->n, p->k, amax + w * kAmaxBlocks);
     };
     auto blocks = [](const AmaxSide &a) {
-        return (unsigned)std::min<int64_t>((a.rows * ((a.k + 2047) / 2048) + 3) / 4, kAmaxBlocks);
+        constexpr int64_t per = kAmaxRun * (kThreads / kWave);
+        return (unsigned)std::min<int64_t>((a.total + per - 1) / per, kAmaxBlocks);
     };
     const AmaxSide x = side(which, X, ldx), y = Y ? side(1, Y, ldy) : x;
     const unsigned nx = blocks(x), ny = Y ? blocks(y) : 0;
