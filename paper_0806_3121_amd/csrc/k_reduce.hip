@@ -1252,27 +1252,54 @@ __device__ inline void vcol_finish(const VerifyArgs &a, const T *C, int64_t blk,
 }
 
 // Row relation (i, c): sum_{h<Gc} C[i, h*bc + c] - sum_{s<S} C[i, n + s*bc + c]
+__device__ inline void finish_row_total(const VerifyArgs &a, int64_t i, int64_t c, double s, double tot, double &ratio,
+                                        unsigned long long &excl) {
+    if (row_rel_erased(a.er, i, c, a.bc)) { excl++; return; }
+    ratio = fmax(ratio, record(a.rep, false, i, c, s - tot, tau_row(a, i, c, tot)));
+}
 template <typename T>
 __device__ inline void finish_row(const VerifyArgs &a, const T *C, int64_t i, int64_t c, double s, double &ratio,
                                   unsigned long long &excl) {
     double tot = 0.0;
     for (int64_t q = 0; q < a.S; ++q) tot += elem<T>::load(C + i * a.ldc + a.n + q * a.bc + c);
-    if (row_rel_erased(a.er, i, c, a.bc)) { excl++; return; }
-    ratio = fmax(ratio, record(a.rep, false, i, c, s - tot, tau_row(a, i, c, tot)));
+    finish_row_total(a, i, c, s, tot, ratio, excl);
 }
 
-// One thread per row relation; lanes take consecutive c (coalesced when bc >= 64).
-template <typename T>
+// One thread per V row relations of consecutive residues (V > 1: 16-byte rows
+// and bc a multiple of V); lanes take consecutive residues (coalesced when
+// bc >= 64 V), four loads in flight.  HBM-bound: a load per relation kept the
+// lanes waiting (both directions of a 264704 x 1024 binary32 C_f with blocks of
+// 256: 860 us with one residue per thread, 555 with four).
+template <typename T, int V>
 __device__ inline void vrow_strided(const VerifyArgs &a, const T *C, int64_t blk, int64_t nblk) {
-    const int64_t total = a.M * a.bc;
+    const int64_t cv = a.bc / V, total = a.M * cv;
     double ratio = 0.0;
     unsigned long long excl = 0;
     for (int64_t t = blk * kThreads + threadIdx.x; t < total; t += nblk * kThreads) {
-        int64_t i = t / a.bc, c = t - i * a.bc;
+        const int64_t i = t / cv, c = (t - i * cv) * V;
         const T *p = C + i * a.ldc + c;
-        double s = 0.0;
-        for (int64_t h = 0; h < a.Gc; ++h) s += elem<T>::load(p + h * a.bc);
-        finish_row<T>(a, C, i, c, s, ratio, excl);
+        double s[V] = {}, tot[V] = {};
+        auto sum = [&](double *d, int64_t h, int64_t n) {
+            for (; h + 3 < n; h += 4) {
+                double w[4][V];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) load_c<T, V>(p + (h + u) * a.bc, w[u]);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int q = 0; q < V; ++q) d[q] += w[u][q];
+            }
+            for (; h < n; ++h) {
+                double w[V];
+                load_c<T, V>(p + h * a.bc, w);
+#pragma unroll
+                for (int q = 0; q < V; ++q) d[q] += w[q];
+            }
+        };
+        sum(s, 0, a.Gc);
+        sum(tot, a.Gc, a.Gc + a.S);                        // the carried columns follow the data columns
+#pragma unroll
+        for (int q = 0; q < V; ++q) finish_row_total(a, i, c + q, s[q], tot[q], ratio, excl);
     }
     fold_block(ratio, excl, &a.rep->max_ratio_r, &a.rep->n_excl_r);
 }
@@ -1306,17 +1333,19 @@ __device__ inline void vrow_block(const VerifyArgs &a, const T *C, int64_t blk, 
     fold_block(ratio, excl, &a.rep->max_ratio_r, &a.rep->n_excl_r);
 }
 
-// The same with 16-byte loads (aligned rows): a wave per row, four loads in
-// flight.  A lane's V columns keep their residues from load to load (64 V is a
-// multiple of bc), so it holds V sums, folded at the end within the lane
-// (bc < V) and across the lanes that share them; lane l < max(1, bc / V) then
-// finishes residues l V + q.
-template <typename T, int V>
+// The same with 16-byte loads (aligned rows): a wave per row, or the block's four
+// waves (WR = 4) where few rows are long, four loads in flight per lane.  A
+// lane's V columns keep their residues from load to load (64 V is a multiple of
+// bc), so it holds V sums, folded at the end within the lane (bc < V) and across
+// the lanes that share them; lane c < bc then finishes residue c.
+template <typename T, int V, int WR>
 __device__ inline void vrow_wave(const VerifyArgs &a, const T *C, int64_t blk, int64_t nblk) {
-    const int lane = threadIdx.x % kWave, bc = (int)a.bc;
+    constexpr int NW = kThreads / kWave, RB = NW / WR, STEP = WR * kWave * V;       // rows per block; columns per load
+    __shared__ double sh[WR > 1 ? NW : 1][kWave];
+    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave, bc = (int)a.bc;
     double ratio = 0.0;
     unsigned long long excl = 0;
-    for (int64_t i = blk * (kThreads / kWave) + threadIdx.x / kWave; i < a.M; i += nblk * (kThreads / kWave)) {
+    for (int64_t i = blk * RB + w / WR; i < a.M; i += nblk * RB) {
         const T *row = C + i * a.ldc;
         double s[V] = {}, v[4][V];
         // a vector that starts before n stays inside its row; its elements at n and beyond are not summed
@@ -1324,30 +1353,42 @@ __device__ inline void vrow_wave(const VerifyArgs &a, const T *C, int64_t blk, i
 #pragma unroll
             for (int q = 0; q < V; ++q) s[q] += j + q < a.n ? x[q] : 0.0;
         };
-        int64_t j = (int64_t)lane * V;
-        for (; j + 3 * kWave * V < a.n; j += 4 * kWave * V) {
+        int64_t j = (int64_t)(w % WR * kWave + lane) * V;
+        for (; j + 3 * STEP < a.n; j += 4 * STEP) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) load_c<T, V>(row + j + u * kWave * V, v[u]);
+            for (int u = 0; u < 4; ++u) load_c<T, V>(row + j + u * STEP, v[u]);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) add(v[u], j + u * kWave * V);
+            for (int u = 0; u < 4; ++u) add(v[u], j + u * STEP);
         }
-        for (; j < a.n; j += kWave * V) {
+        for (; j < a.n; j += STEP) {
             load_c<T, V>(row + j, v[0]);
             add(v[0], j);
         }
-        for (int w = V / 2; w >= bc; w >>= 1) {
+        for (int h = V / 2; h >= bc; h >>= 1) {
 #pragma unroll
             for (int q = 0; q < V / 2; ++q)
-                if (q < w) s[q] += s[q + w < V ? q + w : q];
+                if (q < h) s[q] += s[q + h < V ? q + h : q];
         }
         const int lanes = bc > V ? bc / V : 1;
         for (int off = kWave / 2; off >= lanes; off >>= 1)
 #pragma unroll
             for (int q = 0; q < V; ++q) s[q] += __shfl_xor(s[q], off);
-        if (lane < lanes) {
+        // lane c takes residue c, sum c % V of lane c / V: the stored totals are read side by side, and failed
+        // relations are counted once per wave, not once per sum of a lane
+        double mine = 0.0;
 #pragma unroll
-            for (int q = 0; q < V; ++q)
-                if (q < bc) finish_row<T>(a, C, i, lane * V + q, s[q], ratio, excl);
+        for (int q = 0; q < V; ++q) {
+            const double t = __shfl(s[q], lane / V);
+            if (lane % V == q) mine = t;
+        }
+        if constexpr (WR > 1) {                            // every wave of the block is on this row
+            sh[w][lane] = mine;
+            __syncthreads();
+            if (w == 0 && lane < bc)
+                finish_row<T>(a, C, i, lane, (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]), ratio, excl);
+            __syncthreads();
+        } else if (lane < bc) {
+            finish_row<T>(a, C, i, lane, mine, ratio, excl);
         }
     }
     fold_block(ratio, excl, &a.rep->max_ratio_r, &a.rep->n_excl_r);
@@ -1355,7 +1396,7 @@ __device__ inline void vrow_wave(const VerifyArgs &a, const T *C, int64_t blk, i
 
 // Both directions' relations in one launch: blocks [0, nc) the columns (summed
 // here, or finished from P partitions' sums), the rest the rows.
-enum { ROWS_WAVE, ROWS_BLOCK, ROWS_STRIDED };
+enum { ROWS_WAVE, ROWS_WAVES, ROWS_BLOCK, ROWS_VECTORS, ROWS_STRIDED };
 template <typename T, int V>
 __global__ __launch_bounds__(kThreads) void k_vrelations(const T *C, VerifyArgs a, int64_t P, const double *part,
                                                          unsigned nc, int rows) {
@@ -1365,9 +1406,11 @@ __global__ __launch_bounds__(kThreads) void k_vrelations(const T *C, VerifyArgs 
         return;
     }
     const int64_t blk = blockIdx.x - nc, nblk = gridDim.x - nc;
-    if (V > 1 && rows == ROWS_WAVE) vrow_wave<T, V>(a, C, blk, nblk);
+    if (V > 1 && rows == ROWS_WAVE) vrow_wave<T, V, 1>(a, C, blk, nblk);
+    else if (V > 1 && rows == ROWS_WAVES) vrow_wave<T, V, 4>(a, C, blk, nblk);
     else if (rows == ROWS_BLOCK) vrow_block<T>(a, C, blk, nblk);
-    else vrow_strided<T>(a, C, blk, nblk);
+    else if (V > 1 && rows == ROWS_VECTORS) vrow_strided<T, V>(a, C, blk, nblk);
+    else vrow_strided<T, 1>(a, C, blk, nblk);
 }
 
 // Erasure tests of the one-pass kernel: the residues of each known
@@ -1772,9 +1815,14 @@ static int verify_typed(const abft_problem *p, const T *C, const Erasures &er, c
         else k_vcol_partial<T, 1><<<grid, kThreads, 0, s>>>(C, a, sp, sc.partial);
         nc = (unsigned)(g.br * ((g.N + kWave - 1) / kWave));
     }
-    const int rows = g.bc < 64 && kThreads % g.bc == 0 ? (vec ? ROWS_WAVE : ROWS_BLOCK) : ROWS_STRIDED;
-    const unsigned nr = rows == ROWS_STRIDED ? blocks(g.M * g.bc)
-                        : (unsigned)std::min<int64_t>(rows == ROWS_WAVE ? (g.M + 3) / 4 : g.M, 4096);
+    // the block's waves share a row where a wave per row leaves most of the device idle over rows that take each
+    // wave four rounds of its loads and more
+    const bool few = g.M <= 1024 && g.n >= 4 * 4 * kWave * VV;
+    const int rows = g.bc < 64 && kThreads % g.bc == 0 ? (vec ? (few ? ROWS_WAVES : ROWS_WAVE) : ROWS_BLOCK)
+                     : (vec && g.bc % VV == 0 ? ROWS_VECTORS : ROWS_STRIDED);
+    const unsigned nr = rows == ROWS_STRIDED || rows == ROWS_VECTORS
+                            ? blocks(g.M * (g.bc / (rows == ROWS_VECTORS ? VV : 1)))
+                            : (unsigned)std::min<int64_t>(rows == ROWS_WAVE ? (g.M + 3) / 4 : g.M, 4096);
     const double *part = sp.direct ? nullptr : sc.partial;
     if (vec) k_vrelations<T, VV><<<nc + nr, kThreads, 0, s>>>(C, a, sp.P, part, nc, rows);
     else k_vrelations<T, 1><<<nc + nr, kThreads, 0, s>>>(C, a, sp.P, part, nc, rows);
