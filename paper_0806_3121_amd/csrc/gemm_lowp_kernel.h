@@ -33,7 +33,12 @@ struct Bf16Ops {
 // output tile over 64 k per instruction.  Lane l holds row (column) l % 32 and
 // 32 bytes of k, lanes 32-63 the second half of the 64; accumulator value v of
 // lane l is row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 (measured on
-// gfx950 with integer-valued data, whose products and sums are exact).
+// gfx950 with integer-valued data, whose products and sums are exact).  The 64
+// products of an instruction share its sum's window; against 32-deep groups
+// (v_mfma_f32_16x16x32_fp8_fp8) the error to binary64 measured the same, 60 random
+// problems each with k from 256 to 16384: root mean square equal to 6 digits for
+// uniform and normal data of both signs, within 0.06 % either way for positive data
+// and within 0.01 % with 1 % outliers of a hundred times the size.
 typedef float v16f __attribute__((ext_vector_type(16)));
 struct Fp8x64Ops {
     typedef uint8_t E;
