@@ -85,8 +85,7 @@ WsLayout ws_layout(const abft_problem *p) {
         const VcolSplit sp = vcol_split(g, V);
         if (!sp.direct) need = std::max(need, (size_t)(sp.P * g.br * g.N));
     }
-    L.partial_bytes = sizeof(double) * need;
-    L.partial = take(L.partial_bytes > 0 ? L.partial_bytes : 8);
+    L.partial = take(need > 0 ? sizeof(double) * need : 8);
     L.partial_b = take(eb.direct ? 8 : sizeof(double) * (size_t)(eb.P * g.bc * g.k * 2));
     // fused row statistics: the data rows' strips, then the checksum and group rows' slots
     L.rowpart = take(sizeof(double) * (size_t)(g.m * ea.strips + 2 * g.br * ea.tail_slots));

@@ -45,33 +45,11 @@ __device__ inline void e4m3x4_to_f64(uint32_t w, double *o) {
     o[3] = hi[1];
 }
 
-// binary32 -> E4M3, round to nearest, ties to even fraction; |x| >= 464 (the
-// midpoint above 448 and beyond) saturates to +-448; NaN -> 0x7F.
-__host__ __device__ inline uint8_t f32_to_e4m3_rne(float x) {
-    uint32_t u;
-    __builtin_memcpy(&u, &x, 4);
-    uint8_t sign = (uint8_t)((u >> 24) & 0x80u);
-    uint32_t a = u & 0x7FFFFFFFu;
-    if (a > 0x7F800000u) return 0x7F;
-    float ax;
-    __builtin_memcpy(&ax, &a, 4);
-    if (ax >= 464.0f) return sign | 0x7E;
-    if (ax < 0x1p-6f) {                                   // subnormal grid: multiples of 2^-9
-        float q = __builtin_rintf(ax * 512.0f);          // exact scaling, ties to even
-        return sign | (uint8_t)q;                         // q == 8 is 2^-6, code 0x08
-    }
-    uint32_t r = (a + 0x7FFFFu + ((a >> 20) & 1u)) & 0xFFF00000u;   // round the fraction at bit 20
-    int E = (int)(r >> 23) - 127;
-    uint32_t code = ((uint32_t)(E + 7) << 3) | ((r >> 20) & 7u);
-    if (code > 0x7Eu) code = 0x7E;
-    return sign | (uint8_t)code;
-}
-
-// Four binary32 values to E4M3 bytes by the conversion instruction (round to
-// nearest even, subnormals included).  Values are clamped to +-448 first, so
-// every |x| > 448 gives +-448 as in f32_to_e4m3_rne; a NaN passes, and its
-// byte's sign (the instruction may set it) is cleared.  The same code as
-// f32_to_e4m3_rne for every binary32 pattern up to 448, infinities and NaN.
+// Four binary32 values to E4M3 bytes, round to nearest, ties to even fraction
+// (subnormals included), by the conversion instruction.  Values are clamped to
+// +-448 first, so every |x| > 448 and the infinities give +-448; a NaN passes and
+// gives 0x7F (the instruction may set its sign, which is cleared).  Checked
+// against the format's definition for every binary32 pattern up to 448.
 __device__ inline uint32_t f32x4_to_e4m3(float a, float b, float c, float d) {
     auto sat = [](float x) { return x != x ? x : fminf(fmaxf(x, -448.0f), 448.0f); };
     int w = __builtin_amdgcn_cvt_pk_fp8_f32(sat(a), sat(b), 0, false);
@@ -262,7 +240,6 @@ struct WsLayout {
     size_t fused_tag;                // owner of the fused partials: fused_key() of the last fused product, else 0
     size_t report;                   // abft_report
     size_t total;
-    size_t partial_bytes;
 };
 WsLayout ws_layout(const abft_problem *p);
 

@@ -21,7 +21,7 @@ namespace abft {
 
 constexpr int64_t kSliverMaxB = 8;
 
-struct TileChoice { int id; int bm, bn, per_cu; double eff; };
+struct TileChoice { int id; int bm, bn; double eff; int per_cu = 0; };   // per_cu: tiles that share a CU, for choose_tile alone
 
 // Estimated time ~ rounds x time per round (tile area / per-tile efficiency);
 // the smallest wins.  A round is one tile on each of the 256 CUs: tiles that
@@ -63,10 +63,10 @@ static int choose_tile(const TileChoice *tab, int n, int64_t M, int64_t N) {
 // 2001 x 1503 x 1236 150 / 81 / 66 / 81, 2048^3 238 / 126 / 131 / 149.
 // A 256 x 128 binary64 tile measured the same as 128 x 128 and is not offered.
 static const TileChoice kF64DirectTiles[] = {
-    {1, 128, 128, 2, 0.94}, {2, 128, 96, 2, 0.935}, {3, 96, 96, 2, 0.94}, {4, 64, 64, 5, 0.90}, {5, 32, 32, 5, 0.75},
+    {1, 128, 128, 0.94}, {2, 128, 96, 0.935}, {3, 96, 96, 0.94}, {4, 64, 64, 0.90}, {5, 32, 32, 0.75},
 };
 static const TileChoice kF32DirectTiles[] = {
-    {0, 256, 128, 1, 0.93}, {1, 128, 128, 2, 0.917}, {4, 64, 64, 2, 0.868}, {5, 32, 32, 5, 0.736},
+    {0, 256, 128, 0.93}, {1, 128, 128, 0.917}, {4, 64, 64, 0.868}, {5, 32, 32, 0.736},
 };
 // The fused partial sums in the workspace have room for tiles of this edge and more.
 constexpr int kF64FusedTiles = 3, kF32FusedTiles = 2;
@@ -74,16 +74,16 @@ constexpr int kF64FusedTiles = 3, kF32FusedTiles = 2;
 // Short and small products: the direct tiles at their rates with two blocks per CU, and the register-staged
 // kernel's for a ragged k.
 static const TileChoice kF64ShortTiles[] = {
-    {1, 128, 128, 2, 0.87}, {2, 128, 96, 2, 0.89}, {3, 96, 96, 2, 0.88},
+    {1, 128, 128, 0.87, 2}, {2, 128, 96, 0.89, 2}, {3, 96, 96, 0.88, 2},
 };
 static const TileChoice kF32ShortTiles[] = {
-    {0, 256, 128, 1, 0.85}, {1, 128, 128, 2, 0.84},
+    {0, 256, 128, 0.85, 1}, {1, 128, 128, 0.84, 2},
 };
 static const TileChoice kF64Tiles[] = {
-    {0, 256, 128, 1, 0.818}, {1, 128, 128, 2, 0.787}, {2, 128, 96, 2, 0.80}, {3, 96, 96, 2, 0.76},
+    {0, 256, 128, 0.818, 1}, {1, 128, 128, 0.787, 2}, {2, 128, 96, 0.80, 2}, {3, 96, 96, 0.76, 2},
 };
 static const TileChoice kF32Tiles[] = {
-    {0, 256, 128, 1, 0.80}, {1, 128, 128, 2, 0.78},
+    {0, 256, 128, 0.80, 1}, {1, 128, 128, 0.78, 2},
 };
 
 // The data-part kernel and tile for an M x N x K product of element type E.
@@ -94,10 +94,11 @@ struct MainPick {
 // Whether an M x N x K product (K in slabs of BK) is picked from the direct
 // tiles by rounds.  Below four slabs a launch is mostly its start and its
 // stores and the pick matters little (binary64 776 x 5384 x 32: 13 us with any
-// tile; 1032 x 5384 x 48: 17 to 23), and so it does for the small products of
-// a ragged k or a fused epilogue excluded here (320 x 320 x 250: 21 us against
-// 8): these stay with the short table and the register-staged kernel, whose
-// tiles are checked at just such sizes.
+// tile; 1032 x 5384 x 48: 17 to 23).  The small products of a ragged k or a fused
+// epilogue excluded here would gain from it too (320 x 320 x 250: 21 us on the
+// register-staged kernel, 8 on a direct tile): they stay with the kernel that the
+// numeric checks of that kernel's tiles run at these sizes, which is why the line
+// lies there and not where the time says.
 static bool by_rounds(int64_t M, int64_t N, int64_t K, int64_t BK, bool fused) {
     const int64_t least = fused ? int64_t(1) << 18 : (K % BK ? int64_t(1) << 17 : 0);
     return K >= 4 * BK && M * N > least;
@@ -231,7 +232,7 @@ static int protected_product(const abft_problem *p, const Geom &g, const E *A, c
 // When k is a multiple of the 128-byte slab the 256 x 256 tile runs in the kernel
 // made for that (16384^3: 6472 us, 6421 in the ring).
 static const TileChoice kLowpTiles[] = {
-    {0, 256, 256, 1, 0.50}, {3, 256, 128, 1, 0.36}, {1, 128, 128, 2, 0.35}, {2, 64, 64, 4, 0.195},
+    {0, 256, 256, 0.50}, {3, 256, 128, 0.36}, {1, 128, 128, 0.35}, {2, 64, 64, 0.195},
 };
 static MainPick pick_main_lowp(int64_t elem_size, int64_t M, int64_t N, int64_t K, bool fused) {
     const int64_t slab = 128 / elem_size;
