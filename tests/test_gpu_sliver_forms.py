@@ -43,6 +43,7 @@ def test_carried_blocks_are_exact(dev, case):
     A = synth.uniform_ints(SEED, synth.STREAM_A, m, k, -2, 2).astype(np.float64)
     Bt = synth.uniform_ints(SEED, synth.STREAM_B, n, k, -2, 2).astype(np.float64)
     P = abft.Protected(DT[dt], m, n, k, br, bc, device=dev, lam=10.0)
+    assert ("k_corner" in abft.describe_gemm(P.p)) == (lowp and br * bc >= 128 * 128)
     Ad, Btd = (torch.from_numpy(X.astype(np.float64 if dt == "f64" else np.float32)).to(dev) for X in (A, Bt))
     if lowp:
         abft.quantize_encode(P.p, Ad, Btd, P.A, P.Bt, P.ws)
