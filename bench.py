@@ -73,12 +73,12 @@ FLIP_BITS = {"f64": (40, 62), "f32": (24, 29), "bf16": (24, 29), "fp8": (24, 29)
 # WRITE_SIZE on this benchmark, FETCH_SIZE scaled by 2 (a 1 GiB copy reads 0.5 GiB of FETCH_SIZE);
 # summarized in profiles/hbm_traffic_counters_c2_c2b1_c2panel_c2w_c4_c5.txt.  Re-measure when those kernels change.
 TRAFFIC = {
-    "c2": 25.095e9 + 0.679e9,                       # k_gemm_mfma2 (checksum blocks tiled with the data)
-    "c2b1": 14.174e9 + 0.578e9 + 1.075e9,           # k_gemm_mfma2 + the carried row and column
-    "c2panel": 3.444e9 + 0.679e9,                   # one accumulating panel launch of k_gemm_mfma2 (mean of 8)
-    "c2w": 25.378e9 + 0.679e9,                      # k_gemm_mfma2 over the weighted-checksum C_f
-    "c4": 13.572e9 + 1.123e9 + 1.076e9,             # k_gemm_lowp2 + the carried row and column
-    "c5": 4.313e9 + 2.647e9 + 0.225e9 + 0.087e9,    # kb_gemm (the chosen 256 x 256 launch) + kb_combine
+    "c2": 25.468e9 + 0.679e9,                       # k_gemm_mfma2 (checksum blocks tiled with the data)
+    "c2b1": 14.558e9 + 0.578e9 + 1.075e9,           # k_gemm_mfma2 + the carried row and column
+    "c2panel": 3.464e9 + 0.679e9,                   # one accumulating panel launch of k_gemm_mfma2 (mean of 8)
+    "c2w": 25.696e9 + 0.679e9,                      # k_gemm_mfma2 over the weighted-checksum C_f
+    "c4": 13.391e9 + 1.123e9 + 1.076e9,             # k_gemm_lowp2 + the carried row and column
+    "c5": 4.293e9 + 2.648e9 + 0.225e9 + 0.087e9,    # kb_gemm (the chosen 256 x 256 launch) + kb_combine
 }
 SEED = 20080523
 # bound on max|C - C_oracle| / max|C_oracle| for the reported oracle check: binary64 as the parity tests;
