@@ -224,8 +224,11 @@ static int protected_product(const abft_problem *p, const Geom &g, const E *A, c
 // offered to a fused epilogue, whose sums have no room for it.  Below eight slabs
 // of k, where a launch is mostly its start and stores, it is the tile of products
 // no wider than itself (bfloat16 299247 x 26 x 32: 19 us, 128x128 29, FP8 16 x
-// 289750 x 352: 24 and 33) and not offered to others (FP8 500 x 600 x 528: 10.9 us
-// with either small tile).
+// 289750 x 352: 24 and 33) -- in FP8, whose 128 bytes are more of k, below four
+// slabs of those up to 192 wide too (164827 x 65 x 192: 23 us, 256x128 30;
+// 269714 x 162 x 144 48 and 70, 93 x 164860 x 336 27 and 32; but 163 x 45118 x 896
+// 29 and 22, and in bfloat16 166 x 170184 x 328 75 and 60) -- and not offered to
+// others (FP8 500 x 600 x 528: 10.9 us with either small tile).
 // A whole number of rounds away the order moves with k and the rows' alignment by a
 // few percent only (68015 x 1008 x 752: 183 / 189 / 184); 128x128 needs three rounds
 // and more to come near its rate (4913 x 2276 x 2976: 93 us, 256x256 77).
@@ -237,7 +240,8 @@ static const TileChoice kLowpTiles[] = {
 static MainPick pick_main_lowp(int64_t elem_size, int64_t M, int64_t N, int64_t K, bool fused) {
     const int64_t slab = 128 / elem_size;
     const bool brief = K < 8 * slab;
-    if (brief && !fused && std::min(M, N) <= 64) return {false, &kLowpTiles[3]};
+    const int64_t narrow = elem_size == 1 && K < 4 * slab ? 192 : 64;
+    if (brief && !fused && std::min(M, N) <= narrow) return {false, &kLowpTiles[3]};
     const TileChoice *t = &kLowpTiles[choose_rounds(kLowpTiles, fused || brief ? 3 : 4, M, N)];
     return {t->bm == 256 && t->bn == 256 && K % slab == 0, t};
 }
