@@ -74,7 +74,11 @@ inline SliverExtra sliver_extra(const int *scale_exp, bool accumulate) {
 }
 
 // NR rows of X per wave, NY >= R rows of Y (rows at and past R repeat the last,
-// and are not stored), UK chunks of k per lane in a step.
+// and are not stored), UK chunks of k per lane in a step.  Every count of rows has
+// an NY of its own: the checksum rows' reads from L2 and their widening are most
+// of the work (five rows in eight places and in five, us, whole products: FP8
+// 120 x 71585 x 1376 260 and 174, bfloat16 125 x 53450 x 792 84 and 65, binary64
+// 25 x 36170 x 262 52 and 43).
 template <typename TX, typename TY, typename TC, int NR, int NY, int UK, bool NT>
 __device__ __attribute__((always_inline)) inline void sliver_rows(const SliverJob<TX, TY, TC> &j, double scale,
                                                                   bool accumulate, int64_t block) {
@@ -164,13 +168,13 @@ __device__ __attribute__((always_inline)) inline void sliver_rows(const SliverJo
         // the NR NY sums over the lanes by a reduce-scatter: each exchange halves the sums a lane holds until one
         // is left, then a butterfly within the lanes that share it -- per sum the same additions as a butterfly
         // over the wave, with about a fifth of the exchanges for eight sums (what a short k spends its time on)
-        constexpr int NS = NR * NY;
+        constexpr int NYP = NY <= 2 ? NY : (NY <= 4 ? 4 : 8), NS = NR * NYP;
         static_assert((NS & (NS - 1)) == 0 && NS <= 64, "a power of two");
         double v[NS];
 #pragma unroll
         for (int r = 0; r < NR; ++r)
 #pragma unroll
-            for (int y = 0; y < NY; ++y) v[r * NY + y] = acc[r][y];
+            for (int y = 0; y < NYP; ++y) v[r * NYP + y] = y < NY ? acc[r][y < NY ? y : 0] : 0.0;
 #pragma unroll
         for (int off = 32, h = NS / 2; off > 0; off >>= 1, h >>= 1) {
             if (h > 0) {
@@ -184,7 +188,7 @@ __device__ __attribute__((always_inline)) inline void sliver_rows(const SliverJo
                 v[0] += __shfl_xor(v[0], off, 64);
             }
         }
-        const int e = lane / (64 / NS), r = e / NY, y = e % NY;
+        const int e = lane / (64 / NS), r = e / NYP, y = e % NYP;
         if (lane % (64 / NS) == 0 && u0 + r < j.U && y < j.R)
             store_out<TC>(j.out + (u0 + r) * j.ou + y * j.os, scale * v[0], accumulate);
     }
@@ -248,7 +252,7 @@ __device__ __attribute__((always_inline)) inline void sliver_launch(const Sliver
     sliver_rows<TX, TY, TC, NR, NY, UK, NT>(first ? a : b, scale, x.accumulate != 0, first ? blk : blk - a.blocks);
 }
 template <typename TX, typename TY, typename TC, int NY, bool NT>
-__global__ __launch_bounds__(kSliverThreads, sizeof(TX) == 1 && NY == 8 ? 2 : 4) void k_sliver(SliverJob<TX, TY, TC> a, SliverJob<TX, TY, TC> b,
+__global__ __launch_bounds__(kSliverThreads, sizeof(TX) == 1 && NY >= 6 ? 2 : 4) void k_sliver(SliverJob<TX, TY, TC> a, SliverJob<TX, TY, TC> b,
                                                           SliverExtra x) {
     constexpr int V = vec16<TX>::N > vec16<TY>::N ? vec16<TX>::N : vec16<TY>::N;
     // chunks of k per lane in a step, fewer where more rows of Y hold registers
@@ -311,7 +315,11 @@ inline int slivers(SliverJob<TX, TY, TC> a, const SliverJob<TX, TY, TC> *b, cons
         auto by_ny = [&](auto st) {
             if (R == 1) go(std::integral_constant<int, 1>{}, st);
             else if (R == 2) go(std::integral_constant<int, 2>{}, st);
-            else if (R <= 4) go(std::integral_constant<int, 4>{}, st);
+            else if (R == 3) go(std::integral_constant<int, 3>{}, st);
+            else if (R == 4) go(std::integral_constant<int, 4>{}, st);
+            else if (R == 5) go(std::integral_constant<int, 5>{}, st);
+            else if (R == 6) go(std::integral_constant<int, 6>{}, st);
+            else if (R == 7) go(std::integral_constant<int, 7>{}, st);
             else go(std::integral_constant<int, 8>{}, st);
         };
         nt ? by_ny(std::true_type{}) : by_ny(std::false_type{});

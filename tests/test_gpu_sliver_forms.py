@@ -1,5 +1,5 @@
 """GPU test of the carried blocks' forms: every count of checksum rows a launch
-groups (1, 2, 4, 8 and a remainder), the corner entry by entry and by tiles
+takes (one to eight, and a remainder), the corner entry by entry and by tiles
 (ragged in both directions), several operand rows per wave with k of one short
 chunk and of more, in every element type.
 
